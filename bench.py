@@ -74,6 +74,8 @@ def log(*a):
 
 def _kernel_file(kernel_cfg: int) -> str:
     """The source file that defines the main kernel of a configuration id."""
+    if kernel_cfg >= 2000:
+        return "herk64.hpp"
     if 180 <= kernel_cfg < 200:
         return "wide.hpp"
     if kernel_cfg >= 100:

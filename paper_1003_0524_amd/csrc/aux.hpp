@@ -271,10 +271,12 @@ struct ReduceArgs {
 // (one round of loads for up to 6 RED_SG slots), the groups are added in order.
 constexpr int RED_SG = 16;
 
-// Position of G[row][col] of Gram tile tp in a partial slot written as
-// [tile][element i][lane] (see acc_row for the two accumulator layouts).
+// Position of G[band c, part p][band c2, part p2] of Gram tile tp in a partial slot written as
+// [tile][element i][lane] (see acc_row for the two accumulator layouts). Rows and columns of a tile:
+// 8 part + band, or (ACC64 = 2, herk64_kernel) 2 band + part.
 template <int ACC64>
-__device__ __forceinline__ int gidx(int tp, int row, int col) {
+__device__ __forceinline__ int gidx(int tp, int c, int p, int c2, int p2) {
+  const int row = ACC64 == 2 ? 2 * c + p : c + 8 * p, col = ACC64 == 2 ? 2 * c2 + p2 : c2 + 8 * p2;
   return ACC64 ? (tp * 4 + (row >> 2)) * 64 + col + 16 * (row & 3)
                : (tp * 4 + (row & 3)) * 64 + col + 16 * (row >> 2);
 }
@@ -293,8 +295,8 @@ __global__ __launch_bounds__(64 * RED_SG) void reduce_kernel(ReduceArgs a) {
   const int e = threadIdx.x & 63, sg = threadIdx.x >> 6;
   const int c = e & 7, c2 = e >> 3;
   const int n = I * 8 + c, n2 = J * 8 + c2;
-  const int irr = gidx<ACC64>(tp, c, c2), iii = gidx<ACC64>(tp, c + 8, c2 + 8);
-  const int iri = gidx<ACC64>(tp, c, c2 + 8), iir = gidx<ACC64>(tp, c + 8, c2);
+  const int irr = gidx<ACC64>(tp, c, 0, c2, 0), iii = gidx<ACC64>(tp, c, 1, c2, 1);
+  const int iri = gidx<ACC64>(tp, c, 0, c2, 1), iir = gidx<ACC64>(tp, c, 1, c2, 0);
   double re = 0.0, im = 0.0, dg = 0.0;
   // slots sg, sg + RED_SG, ... in order; UN slots' loads are issued before their adds,
   // unconditionally: a slot past the end reads the last slot of k and weighs it by zero

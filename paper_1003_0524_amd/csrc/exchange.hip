@@ -13,6 +13,7 @@
 #include <cstring>
 #include <mutex>
 #include <numeric>
+#include <queue>
 #include <string>
 #include <vector>
 
@@ -21,6 +22,7 @@
 #include "tile.hpp"
 #include "fused.hpp"
 #include "wide.hpp"
+#include "herk64.hpp"
 #include "gamma.hpp"
 #include "backx.hpp"
 #include "plain.hpp"
@@ -75,13 +77,6 @@ struct KernelCfg {
 // form stages two FP64 operands per row block and therefore stops at n_b <= 64.
 const KernelCfg kCfgs[] = {
     CFG(M_F64, 0, 64, 16, 6, 3, 4, 1, 2, 0),       CFG(M_F64, 0, 64, 16, 8, 8, 4, 1, 2, 1),
-    // FP64 HERK: the column tiles split over two (eight wavefronts, two per SIMD) or, for 12
-    // band tiles, three (twelve wavefronts, 159 registers; 7 % faster than eight); the
-    // four-wavefront instances of the same tiles were 22-29 % slower; 13 band tiles run as 14
-    // (one padding tile)
-    CFG(M_F64, 1, 64, 16, 12, 3, 4, 3, 2, 18),
-    CFG(M_F64, 1, 64, 16, 12, 3, 4, 2, 2, 14),     CFG(M_F64, 1, 64, 16, 8, 8, 4, 2, 2, 15),
-    CFG(M_F64, 1, 64, 16, 14, 13, 4, 2, 2, 17),    CFG(M_F64, 1, 64, 16, 16, 16, 4, 2, 2, 16),
     CFG(M_F32, 1, 128, 16, 12, 3, 4, 2, 2, 20),    CFG(M_F32, 1, 128, 16, 8, 8, 4, 2, 2, 21),
     CFG(M_F32, 1, 64, 16, 13, 13, 4, 1, 2, 23),   CFG(M_F32, 1, 128, 16, 16, 16, 4, 2, 2, 22),
     CFG(M_BF16X3, 1, 128, 32, 12, 3, 4, 2, 2, 30), CFG(M_BF16X3, 1, 128, 32, 8, 8, 4, 2, 2, 31),
@@ -162,6 +157,25 @@ const FusedKCfg kFused[] = {
     WCFG(M_F32, 8, 2, 189),            WCFG(M_BF16X3, 8, 2, 190),         WCFG(M_BF16X6, 8, 2, 191),
 };
 
+// FP64 Cholesky/HERK kernels (herk64.hpp): nbt band tiles, ng n'' values per pass. The planner picks
+// the smallest nbt that holds the context's bands and the ng of the cheapest plan (build_plan64).
+struct Herk64K {
+  int nbt, ng, nw, npw, ctw;
+  void (*fn)(Herk64Args);           // complex128 M
+  void (*fn64)(Herk64Args);         // complex64 M
+  int id() const { return 2000 + 16 * nbt + ng; }
+};
+#define HCFG(NBT, NG)                                                                              \
+  Herk64K{NBT, NG, Herk64Cfg<NBT, NG, false>::NW, Herk64Cfg<NBT, NG, false>::NPW,                   \
+          Herk64Cfg<NBT, NG, false>::CTW, herk64_kernel<NBT, NG, false>, herk64_kernel<NBT, NG, true>}
+const Herk64K kHerk64[] = {
+    HCFG(1, 1), HCFG(1, 2), HCFG(1, 4), HCFG(1, 8), HCFG(1, 12),
+    HCFG(2, 1), HCFG(2, 2), HCFG(2, 3), HCFG(2, 4), HCFG(2, 6),
+    HCFG(3, 1), HCFG(3, 2), HCFG(3, 3), HCFG(3, 4),
+    HCFG(4, 1), HCFG(4, 2), HCFG(5, 1), HCFG(6, 1), HCFG(7, 1), HCFG(8, 1),
+    HCFG(9, 1), HCFG(10, 1), HCFG(11, 1), HCFG(12, 1), HCFG(13, 1), HCFG(14, 1), HCFG(15, 1), HCFG(16, 1),
+};
+
 struct Plan {
   std::vector<WorkItem> items;      // generation order: pair-major, slot = index
   std::vector<int> pair_item;       // [n_pairs + 1] item range per pair
@@ -176,6 +190,9 @@ struct Plan {
   int32_t* d_slot_begin = nullptr;
   double* d_slot_w = nullptr;
   int n_slots = 0;
+  const Herk64K* h64 = nullptr;     // FP64 HERK: the kernel of this plan
+  WorkItem* d_order = nullptr;      //  its items in launch order (padding items: pair -1)
+  std::vector<int> order_begin;     //  [launches + 1]: every k at once, or one launch per k or pair
 };
 
 }  // namespace
@@ -226,7 +243,8 @@ struct exc_ctx {
   std::vector<double> pair_w;
   double* d_pair_w = nullptr;
   int32_t* d_pair_begin = nullptr;
-  Plan plain, bat;
+  Plan plain, bat, perk;              // perk: FP64 HERK, one launch per k (bat when there is one k)
+  bool h64 = false;                   // FP64 Cholesky/HERK through herk64_kernel
   const KernelCfg* cfg = nullptr;
   const FusedKCfg* fcfg = nullptr;    // non-null: reduced-precision HERK through the fused kernel
   bool fused = false;
@@ -379,8 +397,10 @@ int npieces(int mode) { return mode == M_BF16X3 ? 2 : (mode == M_BF16X6 ? 3 : 1)
 void free_plan(Plan& p) {
   hipFree(p.d_items); hipFree(p.d_items_lpt); hipFree(p.d_slot_begin); hipFree(p.d_slot_w);
   hipFree(p.d_items_xq); hipFree(p.d_qbeg);
-  p.d_items = p.d_items_lpt = p.d_items_xq = nullptr; p.d_slot_begin = nullptr; p.d_slot_w = nullptr;
+  hipFree(p.d_order);
+  p.d_items = p.d_items_lpt = p.d_items_xq = p.d_order = nullptr; p.d_slot_begin = nullptr; p.d_slot_w = nullptr;
   p.d_qbeg = nullptr;
+  p.n_slots = 0;
 }
 
 void release_timing(exc_ctx* c) {
@@ -418,6 +438,7 @@ void release(exc_ctx* c) {
   for (void* p : ptrs) if (p) hipFree(p);
   free_plan(c->plain);
   free_plan(c->bat);
+  free_plan(c->perk);
 }
 
 // Dense rows per row block of a fused or wide instance (its row parts when items are
@@ -578,6 +599,194 @@ exc_status build_plan(exc_ctx* c, Plan& P, int split_rows) {
   return EXC_OK;
 }
 
+// ---------------------------------------------------------------------------
+// Work items of the FP64 Cholesky/HERK kernel. An item is a pair, a run of n'' values and a run of
+// row parts (part 0 the block-sparse rows, part 1 + j the dense rows [64 j, 64 j + 64)); costs are in
+// matrix instructions of one wavefront (64 cycles each).
+// ---------------------------------------------------------------------------
+struct Split64 {
+  const Herk64K* k = nullptr;
+  int passes = 1;                   // n'' passes per item (0: all)
+  int groups = 1;                   // runs of row parts per pair (0: one item per part)
+};
+
+double part_cost64(const exc_ctx* c, const Herk64K& k, const PairInfo& p, int part) {
+  const bool regg = k.nbt <= 3;
+  const int npt = k.nbt * (k.nbt + 1) / 2;
+  if (part == 0) return (double)((c->n_s + 15) / 16) * std::max(10, regg ? k.ng * npt : 4 * k.npw * k.ng);
+  const int np = (p.nd - 64 * (part - 1) + 15) / 16;
+  // (a panel shorter than its barrier and loads costs those)
+  return (double)np * std::max(12, 8 * k.ctw) + (regg ? 4 * k.ng * npt : 16 * k.npw * k.ng + 12);
+}
+
+// The items of one pair under a split, through push(g0, g1, part0, part1, cost).
+template <class F>
+void split_pair64(const exc_ctx* c, const Split64& sp, const PairInfo& p, F&& push) {
+  const Herk64K& k = *sp.k;
+  const int nparts = 1 + (p.nd + 63) / 64, first = c->n_s > 0 ? 0 : 1;
+  const int npass = (c->n_occ + k.ng - 1) / k.ng, per = sp.passes ? sp.passes : npass;
+  std::vector<double> pc(nparts, 0.0);
+  double tot = 0.0;
+  for (int i = first; i < nparts; ++i) tot += pc[i] = part_cost64(c, k, p, i);
+  for (int g = 0; g < npass; g += per) {
+    const int n = std::min(per, npass - g), g0 = g * k.ng, g1 = std::min(c->n_occ, (g + n) * k.ng);
+    int at = first;
+    double left = tot;
+    for (int r = sp.groups ? sp.groups : nparts; at < nparts; --r) {
+      // the next run: parts until its share of what is left is reached
+      const double want = r > 1 ? left / r : 1e300;
+      double cs = pc[at];
+      int e = at + 1;
+      while (e < nparts && sp.groups && cs + 0.5 * pc[e] <= want) cs += pc[e++];
+      push(g0, g1, at, e, cs * n);
+      left -= cs;
+      at = e;
+    }
+  }
+}
+
+// Launch order: the hardware deals workgroup b to XCD b mod 8. Items of one q share its factor, so q are
+// dealt to eight lists by decreasing cost, each list in order of decreasing cost, the lists interleaved (and
+// padded); where few q leave the lists uneven, one list over all items instead.
+void order64(const exc_ctx* c, const std::vector<WorkItem>& it, const std::vector<double>& cost, int i0, int i1,
+             std::vector<WorkItem>& out) {
+  std::vector<int> ord(i1 - i0);
+  std::iota(ord.begin(), ord.end(), i0);
+  std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return cost[a] > cost[b]; });
+  std::vector<double> qc(c->n_q, 0.0), load(8, 0.0);
+  for (int i : ord) qc[c->pairs[it[i].pair].q] += cost[i];
+  std::vector<int> qo(c->n_q), qof(c->n_q, 0);
+  std::iota(qo.begin(), qo.end(), 0);
+  std::stable_sort(qo.begin(), qo.end(), [&](int a, int b) { return qc[a] > qc[b]; });
+  double tot = 0.0;
+  for (int q : qo) {
+    const int b = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+    qof[q] = b;
+    load[b] += qc[q];
+    tot += qc[q];
+  }
+  if (*std::max_element(load.begin(), load.end()) > 1.06 * tot / 8) {
+    for (int i : ord) out.push_back(it[i]);
+    return;
+  }
+  std::vector<std::vector<int>> l(8);
+  for (int i : ord) l[qof[c->pairs[it[i].pair].q]].push_back(i);
+  size_t n = 0;
+  for (const auto& x : l) n = std::max(n, x.size());
+  WorkItem none{};
+  none.pair = -1;
+  for (size_t j = 0; j < n; ++j)
+    for (int b = 0; b < 8; ++b) out.push_back(j < l[b].size() ? it[l[b][j]] : none);
+}
+
+// The split with the smallest estimated time over the pairs [p0, p1): the longest-first schedule of its items on
+// the workgroup slots of the GPU (two per CU; one for more than eight band tiles), each with a fixed overhead, plus
+// the traffic of its partial slots. At most max_slots items (0: no limit beyond 2 GiB of partials); the coarsest
+// split (one item per pair) always qualifies.
+Split64 pick_split64(const exc_ctx* c, int p0, int p1, size_t max_slots, int n_cu) {
+  Split64 best;
+  double best_t = 1e300;
+  const size_t slot_b = (size_t)c->gstride * 8;
+  if (!max_slots) max_slots = std::max<size_t>(p1 - p0, ((size_t)2 << 30) / slot_b);
+  std::vector<double> cs;
+  for (const Herk64K& k : kHerk64) {
+    if (k.nbt != c->nbt_max) continue;
+    const int npass = (c->n_occ + k.ng - 1) / k.ng;
+    const int slots = n_cu * (k.nw == 4 ? 2 : 1);
+    for (int passes : {0, 4, 2, 1}) {
+      if (passes >= npass) continue;
+      for (int groups : {1, 2, 3, 4, 6, 0}) {
+        const Split64 sp{&k, passes, groups};
+        cs.clear();
+        for (int i = p0; i < p1 && cs.size() <= max_slots; ++i)
+          split_pair64(c, sp, c->pairs[i], [&](int, int, int, int, double x) { cs.push_back(x + 100.0); });
+        if (cs.size() > max_slots && !(passes == 0 && groups == 1)) continue;
+        double sum = 0.0, mx = 0.0, t;
+        for (double x : cs) { sum += x; mx = std::max(mx, x); }
+        if (cs.size() > (size_t)32 * slots) {
+          t = sum / slots + 0.5 * mx;
+        } else {
+          std::sort(cs.begin(), cs.end(), std::greater<double>());
+          std::priority_queue<double, std::vector<double>, std::greater<double>> h;
+          for (double x : cs) {
+            double at = 0.0;
+            if ((int)h.size() == slots) { at = h.top(); h.pop(); }
+            h.push(at + x);
+          }
+          t = 0.0;
+          while (!h.empty()) { t = h.top(); h.pop(); }
+        }
+        if (k.nw == 4) t *= 2.0;                       // two workgroups share a CU's matrix cores
+        t += (double)cs.size() * slot_b * 2 / 5e12 * 2.4e9 / 64;
+        if (t < 0.98 * best_t) { best_t = t; best = sp; }
+      }
+    }
+  }
+  return best;
+}
+
+// FP64 plan: `per` = 0 every pair in one launch, 1 one launch per k, 2 one launch per pair.
+exc_status build_plan64(exc_ctx* c, Plan& P, int per, size_t max_slots) {
+  int n_cu = 256;
+  (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device);
+  P.items.clear();
+  P.pair_item.assign(1, 0);
+  P.k_item.assign(1, 0);
+  P.slot_begin.assign(1, 0);
+  P.slot_w.clear();
+  P.order_begin.assign(1, 0);
+  // the split is chosen for all pairs, the k with the most pairs, or the largest pair
+  int a = 0, b = (int)c->pairs.size();
+  if (per == 1) {
+    int km = 0;
+    for (int k = 1; k < c->n_k; ++k)
+      if (c->k_pair[k + 1] - c->k_pair[k] > c->k_pair[km + 1] - c->k_pair[km]) km = k;
+    a = c->k_pair[km];
+    b = c->k_pair[km + 1];
+  } else if (per == 2) {
+    for (int i = 1; i < b; ++i)
+      if (c->pairs[i].nd > c->pairs[a].nd) a = i;
+    b = a + 1;
+  }
+  const Split64 sp = pick_split64(c, a, b, max_slots, n_cu);
+  if (!sp.k) return fail(c, EXC_EUNSUPPORTED, "no FP64 kernel for n_b = %d", c->nb_max);
+  P.h64 = sp.k;
+  std::vector<double> cost;
+  std::vector<WorkItem> order;
+  for (int k = 0; k < c->n_k; ++k) {
+    for (int i = c->k_pair[k]; i < c->k_pair[k + 1]; ++i) {
+      split_pair64(c, sp, c->pairs[i], [&](int g0, int g1, int r0, int r1, double cs) {
+        WorkItem w{};
+        w.pair = i; w.g0 = g0; w.g1 = g1; w.ngc = sp.k->ng; w.rb0 = r0; w.rb1 = r1;
+        w.slot = (int)P.items.size();
+        P.items.push_back(w);
+        P.slot_w.push_back(c->pair_w[i]);
+        cost.push_back(cs);
+      });
+      P.pair_item.push_back((int)P.items.size());
+      if (per == 2) {
+        for (int j = P.pair_item[i]; j < P.pair_item[i + 1]; ++j) order.push_back(P.items[j]);
+        P.order_begin.push_back((int)order.size());
+      }
+    }
+    P.k_item.push_back((int)P.items.size());
+    P.slot_begin.push_back((int)P.items.size());
+    if (per == 1) {
+      order64(c, P.items, cost, P.k_item[k], P.k_item[k + 1], order);
+      P.order_begin.push_back((int)order.size());
+    }
+  }
+  if (per == 0) {
+    order64(c, P.items, cost, 0, (int)P.items.size(), order);
+    P.order_begin.push_back((int)order.size());
+  }
+  P.n_slots = (int)P.items.size();
+  TRY(upload(c, &P.d_order, order));
+  TRY(upload(c, &P.d_slot_begin, std::vector<int32_t>(P.slot_begin.begin(), P.slot_begin.end())));
+  TRY(upload(c, &P.d_slot_w, P.slot_w));
+  return EXC_OK;
+}
+
 // Real-factor instances serve only contexts with a real factor; there they are
 // preferred over the general ones of the same capacity. dtype: the element type of M
 // (-1: not known yet -- instances that read complex64 only are left out).
@@ -688,6 +897,7 @@ FusedArgs fused_args(exc_ctx* c, int dtype) {
 struct MainArgs {
   TileArgs t;
   FusedArgs f;
+  Herk64Args h;
 };
 
 // A configured kernel launch: enqueued directly or added to a graph as a node.
@@ -790,12 +1000,38 @@ void cfg_reduce(exc_ctx* c, const Plan& P, int k0, int nk, ReduceArgs& r, KLaunc
   L.grid = dim3(c->nbt_max * (c->nbt_max + 1) / 2, nk);
   L.block = dim3(64 * RED_SG);
   L.shmem = 0;
-  L.fn = r.acc64 ? (const void*)reduce_kernel<1> : (const void*)reduce_kernel<0>;
+  L.fn = c->h64 ? (const void*)reduce_kernel<2>
+                : (r.acc64 ? (const void*)reduce_kernel<1> : (const void*)reduce_kernel<0>);
   L.arg = &r;
 }
 
+// Launch i of an FP64 plan: its part of the launch order.
+void launch64(exc_ctx* c, const Plan& P, int i, int dtype, int k, Herk64Args& a, KLaunch& L) {
+  a = Herk64Args{};
+  a.pairs = c->d_pairs;
+  a.items = P.d_order + P.order_begin[i];
+  a.n_items = P.order_begin[i + 1] - P.order_begin[i];
+  a.mtab = (const void* const*)c->d_mtab;
+  a.n_s = c->n_s;
+  a.n_occ = c->n_occ;
+  a.U = (const double*)c->d_U;
+  a.ws = (const double2*)ws_base(c, k);
+  a.gpart = c->sv ? (double*)c->sv->gpart : (double*)c->d_gpart;
+  a.gstride = c->gstride;
+  a.tmask = c->d_tmask;
+  L.grid = dim3(a.n_items);
+  L.block = dim3(64 * P.h64->nw);
+  L.shmem = 0;
+  L.fn = dtype == EXC_C64 ? (const void*)P.h64->fn64 : (const void*)P.h64->fn;
+  L.arg = &a;
+}
+
+// The plan of one launch per k, and k's launch in it.
+const Plan& k_plan(const exc_ctx* c) { return c->h64 && c->n_k > 1 ? c->perk : c->bat; }
+
 void cfg_tile(exc_ctx* c, int dtype, int k, const WorkItem* items, int n, bool persistent, MainArgs& m,
               KLaunch& L) {
+  if (c->h64) return launch64(c, c->bat, 0, dtype, k, m.h, L);    // (every pair at once)
   L.grid = dim3(persistent ? std::min(n, c->persist_grid) : n);
   L.shmem = 0;
   if (c->fused) {
@@ -842,13 +1078,22 @@ void launch_tile(exc_ctx* c, int dtype, int k, const WorkItem* items, int n, hip
   (void)enqueue(L, st);
 }
 
+// The main kernel of one k on plan P (k_plan).
+void launch_k(exc_ctx* c, const Plan& P, int dtype, int k, hipStream_t st) {
+  if (!c->h64) return launch_tile(c, dtype, k, P.d_items + P.k_item[k], P.k_item[k + 1] - P.k_item[k], st);
+  Herk64Args a;
+  KLaunch L;
+  launch64(c, P, k, dtype, k, a, L);
+  (void)enqueue(L, st);
+}
+
 // One k, batched over its q: sparse rows of all pairs of k, one tile launch, reduce.
 exc_status run_k_batched(exc_ctx* c, int k, int dtype, hipStream_t st) {
   if (!c->fused) TRY(ensure_ws(c, c->ws_k_bytes));
   const int p0 = c->k_pair[k], p1 = c->k_pair[k + 1];
   launch_sparse(c, dtype, k, p0, p1 - p0, st);
-  const Plan& P = c->bat;
-  launch_tile(c, dtype, k, P.d_items + P.k_item[k], P.k_item[k + 1] - P.k_item[k], st);
+  const Plan& P = k_plan(c);
+  launch_k(c, P, dtype, k, st);
   launch_reduce(c, P, k, 1, st);
   return EXC_OK;
 }
@@ -859,6 +1104,13 @@ exc_status run_k_plain(exc_ctx* c, int k, int dtype, hipStream_t st) {
   const Plan& P = c->plain;
   for (int p = c->k_pair[k]; p < c->k_pair[k + 1]; ++p) {
     launch_sparse(c, dtype, k, p, 1, st);
+    if (c->h64) {
+      Herk64Args a;
+      KLaunch L;
+      launch64(c, P, p, dtype, k, a, L);
+      (void)enqueue(L, st);
+      continue;
+    }
     launch_tile(c, dtype, k, P.d_items + P.pair_item[p], P.pair_item[p + 1] - P.pair_item[p], st);
   }
   launch_reduce(c, P, k, 1, st);
@@ -1008,6 +1260,22 @@ exc_status build_batched_graph(exc_ctx* c, int dtype) {
   return EXC_OK;
 }
 
+// FP64: the most partial slots per k with which every k that the no-allocation call's scratch could hold
+// with one slot per pair still fits it (0: no such k, no limit).
+size_t noalloc_slots(const exc_ctx* c) {
+  size_t most = 0;
+  auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+  for (int k = 0; k < c->n_k; ++k) {
+    const size_t np = c->k_pair[k + 1] - c->k_pair[k];
+    const size_t ws = up((size_t)(c->k_ws_start[k + 1] - c->k_ws_start[k]) * c->ws_elem);
+    const size_t slot = ((size_t)c->gstride + c->dstride) * 8;
+    if (ws + np * slot + 512 > kScratchBytes) continue;
+    const size_t n = std::max(np, (kScratchBytes - ws - 512) / slot);
+    most = most ? std::min(most, n) : n;
+  }
+  return most;
+}
+
 // Switch the context to a main-kernel configuration: a fused instance, or
 // (f == nullptr) the block-sparse + tile kernels. Rebuilds the plans, sizes
 // the partial slots and the persistent grid, allocates or releases the
@@ -1033,10 +1301,17 @@ exc_status configure(exc_ctx* c, const FusedKCfg* f, hipStream_t st) {
   // path, one per (n'' chunk, row block) for one launch per pair
   free_plan(c->plain);
   free_plan(c->bat);
-  c->plain.n_slots = c->bat.n_slots = 0;
-  if (c->batched) TRY(build_plan(c, c->bat, 0));
-  else TRY(build_plan(c, c->plain, 1));
-  const size_t nslot = std::max(c->plain.n_slots, c->bat.n_slots);
+  free_plan(c->perk);
+  if (c->h64) {
+    if (!c->batched) TRY(build_plan64(c, c->plain, 2, 0));
+    else TRY(build_plan64(c, c->bat, 0, c->n_k == 1 ? noalloc_slots(c) : 0));
+    if (c->batched && c->n_k > 1) TRY(build_plan64(c, c->perk, 1, noalloc_slots(c)));
+  } else if (c->batched) {
+    TRY(build_plan(c, c->bat, 0));
+  } else {
+    TRY(build_plan(c, c->plain, 1));
+  }
+  const size_t nslot = std::max({c->plain.n_slots, c->bat.n_slots, c->perk.n_slots});
   const size_t asz = c->precision == EXC_FP64 ? 8 : 4;
   hipFree(c->d_gpart);
   hipFree(c->d_dpart);
@@ -1046,6 +1321,7 @@ exc_status configure(exc_ctx* c, const FusedKCfg* f, hipStream_t st) {
   TRY(dalloc(c, &c->d_dpart, nslot * (size_t)c->dstride));
   HIPCHK(c, hipMemset(c->d_gpart, 0, nslot * c->gstride * asz));
   HIPCHK(c, hipMemset(c->d_dpart, 0, nslot * (size_t)c->dstride * 8));
+  if (c->h64) return EXC_OK;                      // (one workgroup per item: no persistent grid)
   const void* main_fn = c->fused ? (const void*)c->fcfg->fn : (const void*)c->cfg->fn;
   const int main_threads = c->fused ? c->fcfg->nt : 64 * c->cfg->NW();
   hipFuncAttributes fa{};
@@ -1307,8 +1583,9 @@ exc_status exchange_init(const exc_desc* d, const exc_coulomb* cv, void* stream,
   c->nbt_max = (c->nb_max + 7) / 8;
   // the unbatched GEMM form runs one pair at a time through its own kernels (any band count)
   c->plain_gemm = c->form == EXC_FORM_GEMM && !c->batched;
-  c->cfg = pick_cfg(c->precision, c->form, c->nbt_max);
-  if (!c->cfg && !c->plain_gemm) {
+  c->h64 = c->precision == EXC_FP64 && c->form == EXC_FORM_CHOL_HERK;
+  c->cfg = c->h64 ? nullptr : pick_cfg(c->precision, c->form, c->nbt_max);
+  if (!c->cfg && !c->plain_gemm && !c->h64) {
     fail(c, EXC_EUNSUPPORTED, "no tile configuration for n_b = %d%s", c->nb_max,
          c->form == EXC_FORM_GEMM ? " (the batched GEMM form takes at most 64 bands)" : "");
     return bail(EXC_EUNSUPPORTED);
@@ -1693,7 +1970,7 @@ exc_status exchange_matrix_noalloc(exc_ctx* c, int32_t k, const void* M, int32_t
   void* base = c->device >= 0 && c->device < kScratchDevices ? g_scratch_ptr[c->device] : nullptr;
   if (!base) return fail(c, EXC_ESTATE, "no scratch address for device %d", c->device);
   // this k's share of the buffers, each region 256-byte aligned
-  const Plan& P = c->bat;
+  const Plan& P = k_plan(c);
   const int s0 = P.slot_begin[k], ns = P.slot_begin[k + 1] - s0;
   const int p0 = c->k_pair[k], np = c->k_pair[k + 1] - p0;
   const size_t asz = c->precision == EXC_FP64 ? 8 : 4;
@@ -1722,7 +1999,7 @@ exc_status exchange_matrix_noalloc(exc_ctx* c, int32_t k, const void* M, int32_t
   // the reduction reads is written first by this call's kernels: nothing needs clearing)
   c->sv = &v;
   launch_sparse(c, dtype, k, p0, np, st);
-  launch_tile(c, dtype, k, P.d_items + P.k_item[k], P.k_item[k + 1] - P.k_item[k], st);
+  launch_k(c, P, dtype, k, st);
   launch_reduce(c, P, k, 1, st);
   c->sv = nullptr;
   HIPCHK(c, hipGetLastError());
@@ -2015,7 +2292,10 @@ exc_status exchange_query(const exc_ctx* c, int32_t what, double* value) {
     case 0: *value = c->bat.n_slots; return EXC_OK;
     case 1: *value = c->flops_nominal; return EXC_OK;
     case 2: *value = c->flops_exec; return EXC_OK;
-    case 3: *value = c->plain_gemm ? 900 : (c->fused ? c->fcfg->id : (c->cfg ? c->cfg->id : -1)); return EXC_OK;
+    case 3:
+      if (c->h64) *value = (c->batched ? c->bat : c->plain).h64->id();
+      else *value = c->plain_gemm ? 900 : (c->fused ? c->fcfg->id : (c->cfg ? c->cfg->id : -1));
+      return EXC_OK;
     case 4: *value = c->bytes_alg; return EXC_OK;
     case 5:
     case 7: {
