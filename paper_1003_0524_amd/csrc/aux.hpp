@@ -271,12 +271,10 @@ struct ReduceArgs {
 // (one round of loads for up to 6 RED_SG slots), the groups are added in order.
 constexpr int RED_SG = 16;
 
-// Position of G[band c, part p][band c2, part p2] of Gram tile tp in a partial slot written as
-// [tile][element i][lane] (see acc_row for the two accumulator layouts). Rows and columns of a tile:
-// 8 part + band, or (ACC64 = 2, herk64_kernel) 2 band + part.
+// Position of G[row][col] of Gram tile tp in a partial slot written as
+// [tile][element i][lane] (see acc_row for the two accumulator layouts).
 template <int ACC64>
-__device__ __forceinline__ int gidx(int tp, int c, int p, int c2, int p2) {
-  const int row = ACC64 == 2 ? 2 * c + p : c + 8 * p, col = ACC64 == 2 ? 2 * c2 + p2 : c2 + 8 * p2;
+__device__ __forceinline__ int gidx(int tp, int row, int col) {
   return ACC64 ? (tp * 4 + (row >> 2)) * 64 + col + 16 * (row & 3)
                : (tp * 4 + (row & 3)) * 64 + col + 16 * (row >> 2);
 }
@@ -295,8 +293,8 @@ __global__ __launch_bounds__(64 * RED_SG) void reduce_kernel(ReduceArgs a) {
   const int e = threadIdx.x & 63, sg = threadIdx.x >> 6;
   const int c = e & 7, c2 = e >> 3;
   const int n = I * 8 + c, n2 = J * 8 + c2;
-  const int irr = gidx<ACC64>(tp, c, 0, c2, 0), iii = gidx<ACC64>(tp, c, 1, c2, 1);
-  const int iri = gidx<ACC64>(tp, c, 0, c2, 1), iir = gidx<ACC64>(tp, c, 1, c2, 0);
+  const int irr = gidx<ACC64>(tp, c, c2), iii = gidx<ACC64>(tp, c + 8, c2 + 8);
+  const int iri = gidx<ACC64>(tp, c, c2 + 8), iir = gidx<ACC64>(tp, c + 8, c2);
   double re = 0.0, im = 0.0, dg = 0.0;
   // slots sg, sg + RED_SG, ... in order; UN slots' loads are issued before their adds,
   // unconditionally: a slot past the end reads the last slot of k and weighs it by zero
@@ -354,6 +352,59 @@ __global__ __launch_bounds__(64 * RED_SG) void reduce_kernel(ReduceArgs a) {
   if (a.vout && a.vout[k]) {
     double2* O = (double2*)a.vout[k];
     O[n + (long)n2 * nb] = v;
+    if (n != n2) O[n2 + (long)n * nb] = make_double2(-re, im);
+  }
+}
+
+// The q sum over herk64_kernel's slots: the 2 KB of a tile are read as they lie. A workgroup takes element i
+// (rows 4 i .. 4 i + 3 of the tile: re and im of bands 2 i and 2 i + 1 against all 16 columns) of one tile of one k:
+// 16 slot groups of 64 lanes, each lane one value of a slot's 512 contiguous bytes, eight slots' loads issued before
+// their adds; the groups are added in order. Bound by HBM (every partial read once) with many slots and by the
+// latency of the loads with few, so a tile is spread over four workgroups: eight small pairs (one k of 320 slots)
+// 28 -> 6 us, 2592 slots of 36 tiles (191 MB) 128 -> 42 us against reduce_kernel's one workgroup per tile.
+__global__ __launch_bounds__(1024) void reduce64_kernel(ReduceArgs a) {
+  __shared__ double red[16][64];
+  const int k = blockIdx.y, nb = a.k_nb[k], nbt = (nb + 7) >> 3;
+  const int tp = blockIdx.x >> 2, el = blockIdx.x & 3;
+  if (tp >= nbt * (nbt + 1) / 2) return;     // uniform over the workgroup
+  int I, J;
+  tp_to_ij(tp, I, J);
+  const int lane = threadIdx.x & 63, sg = threadIdx.x >> 6;
+  const double* g = (const double*)a.gpart + (tp * 4 + el) * 64 + lane;
+  const int s0 = a.slot_begin[k] + sg, s1 = a.slot_begin[k + 1];
+  constexpr int UN = 8;
+  double t = 0.0;
+  for (int sb = s0; sb < s1; sb += 16 * UN) {
+    double x[UN], wq[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {           // (past the end: the last slot, weight zero)
+      const int s = min(sb + 16 * u, s1 - 1);
+      x[u] = g[(long)s * a.gstride];
+      wq[u] = sb + 16 * u < s1 ? a.slot_w[s] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) t += wq[u] * x[u];
+  }
+  red[sg][lane] = t;
+  __syncthreads();
+  if (sg != 0) return;
+  t = red[0][lane];
+#pragma unroll
+  for (int v = 1; v < 16; ++v) t += red[v][lane];
+  // lane: row 4 el + (lane >> 4) = 2 c + p, column lane & 15 = 2 c2 + p2; the lane of p = p2 = 0 finishes (c, c2)
+  const double ri = __shfl(t, lane + 1), ir = __shfl(t, lane + 16), ii = __shfl(t, lane + 17);
+  const int c = 2 * el + (lane >> 5), c2 = (lane & 15) >> 1;
+  const int n = I * 8 + c, n2 = J * 8 + c2;
+  if ((lane & 17) != 0 || n >= nb || n2 >= nb || n > n2) return;
+  double re = t + ii, im = ri - ir;
+  if (a.real_v || n == n2) im = 0.0;
+  if (n == n2 && n < a.n_occ) re += *a.gshift;
+  double2* V = a.vres + a.v_off[k];
+  V[n + (long)n2 * nb] = make_double2(-re, -im);
+  if (n != n2) V[n2 + (long)n * nb] = make_double2(-re, im);
+  if (a.vout && a.vout[k]) {
+    double2* O = (double2*)a.vout[k];
+    O[n + (long)n2 * nb] = make_double2(-re, -im);
     if (n != n2) O[n2 + (long)n * nb] = make_double2(-re, im);
   }
 }

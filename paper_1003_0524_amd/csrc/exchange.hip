@@ -1000,8 +1000,12 @@ void cfg_reduce(exc_ctx* c, const Plan& P, int k0, int nk, ReduceArgs& r, KLaunc
   L.grid = dim3(c->nbt_max * (c->nbt_max + 1) / 2, nk);
   L.block = dim3(64 * RED_SG);
   L.shmem = 0;
-  L.fn = c->h64 ? (const void*)reduce_kernel<2>
-                : (r.acc64 ? (const void*)reduce_kernel<1> : (const void*)reduce_kernel<0>);
+  L.fn = r.acc64 ? (const void*)reduce_kernel<1> : (const void*)reduce_kernel<0>;
+  if (c->h64) {                                  // (no work counters to clear: one workgroup per item)
+    L.grid.x *= 4;
+    L.block = dim3(1024);
+    L.fn = (const void*)reduce64_kernel;
+  }
   L.arg = &r;
 }
 
