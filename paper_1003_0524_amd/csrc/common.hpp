@@ -5,9 +5,11 @@
 
 namespace exc {
 
+typedef double d2_t __attribute__((ext_vector_type(2)));
 typedef double d4_t __attribute__((ext_vector_type(4)));
 typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+typedef uint32_t u2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
 
 // Product modes (values match exc_precision in include/exchange.h).
@@ -185,6 +187,22 @@ __device__ __forceinline__ OP buf_load(__amdgpu_buffer_rsrc_t r, uint32_t voff, 
 __device__ __forceinline__ void lds_load16(__amdgpu_buffer_rsrc_t r, void* lds, uint32_t voff, uint32_t soff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, (int)voff,
                                            (int)soff, 0, 0);
+}
+
+// Workgroup barrier that orders LDS accesses only: __syncthreads() also waits for every global -> LDS load in
+// flight (vmcnt(0)), which would undo requesting panels ahead of their use. The caller waits for the loads the
+// barrier is to publish itself (vmcnt counts).
+//
+// Two more rules keep such loads in flight. A kernel that issues them keeps all its LDS in one array: with several
+// __shared__ variables the compiler tells their accesses apart, and then makes every read of the array that the
+// loads write wait for all of them (as it does for types without alias information, such as HIP's double2: LDS
+// behind such loads is read as scalars or vector extension types). And every path between a load into registers and its use issues the same number
+// of later loads (past the last panel: loads whose every offset is out of range, which touch no memory): where the
+// paths differ the compiler's wait for the registers is for the path with the fewest, in the end vmcnt(0).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // Values the whole workgroup shares, moved to scalar registers: loads of them

@@ -19,10 +19,8 @@
 
 #include "../../include/exchange.h"
 #include "aux.hpp"
+#include "configs.hpp"
 #include "tile.hpp"
-#include "fused.hpp"
-#include "wide.hpp"
-#include "herk64.hpp"
 #include "gamma.hpp"
 #include "backx.hpp"
 #include "plain.hpp"
@@ -85,96 +83,15 @@ const KernelCfg kCfgs[] = {
     CFG(M_BF16X6, 1, 64, 32, 13, 13, 4, 1, 1, 43), CFG(M_BF16X6, 1, 64, 32, 16, 16, 4, 1, 1, 42),
 };
 
-// Fused reduced-precision HERK kernels: RTW row tiles per wavefront (row
-// blocks of 64 RTW rows), NCT band tiles per pass, NB8M the largest band-tile
-// count per n'' value, KC complex k per K-loop panel.
-// coefficients per multipole-free row staged by the fused kernel (its MAXT)
-constexpr int kRunPad = FusedCfg<M_BF16X3, 1, 1, 1, 32>::MAXT;
-// chunks of multipole-free rows: rows (one per lane), multipole rows, chunks (at most)
-constexpr int kChunkRows = FusedCfg<M_BF16X3, 1, 1, 1, 32>::GR;
-constexpr int kChunkMP = FusedCfg<M_BF16X3, 1, 1, 1, 32>::MPC;
-constexpr int kMaxChunks = FusedCfg<M_BF16X3, 1, 1, 1, 32>::MAXCK;
-
-struct FusedKCfg {
-  int mode, RTW, NCT, NB8M, KC, CB, OCC;
-  void (*fn)(FusedArgs);
-  size_t lds;
-  int id;
-  bool realf = false;               // real factor only (inversion-symmetric contexts)
-  int nt = 256;                     // threads per workgroup
-  bool c64only = false;             // reads complex64 M only (the wide kernel)
-  int gchain = 0, grs = 64, grd = 64;   // binary32 Gram chains: kind, rows per chunk (sparse, dense)
-};
-
-#define FCFG(MODE, RTW, NCT, NB8M, KC, ID)                                                       \
-  FusedKCfg{MODE, RTW, NCT, NB8M, KC, 16, 1, fused_kernel<MODE, RTW, NCT, NB8M, KC, 16, 1>,        \
-            FusedCfg<MODE, RTW, NCT, NB8M, KC, 16, 1>::LDS_B, ID, false, 256, false,                \
-            FusedCfg<MODE, RTW, NCT, NB8M, KC, 16, 1>::GCHAIN, FusedCfg<MODE, RTW, NCT, NB8M, KC, 16, 1>::GR, \
-            FusedCfg<MODE, RTW, NCT, NB8M, KC, 16, 1>::GR}
-// two workgroups per CU: at most 256 registers per lane and half the LDS each
-#define FCFG2(MODE, RTW, NCT, NB8M, ID)                                                          \
-  FusedKCfg{MODE, RTW, NCT, NB8M, 32, 16, 2, fused_kernel<MODE, RTW, NCT, NB8M, 32, 16, 2>,       \
-            FusedCfg<MODE, RTW, NCT, NB8M, 32, 16, 2>::LDS_B, ID, false, 256, false,               \
-            FusedCfg<MODE, RTW, NCT, NB8M, 32, 16, 2>::GCHAIN, FusedCfg<MODE, RTW, NCT, NB8M, 32, 16, 2>::GR, \
-            FusedCfg<MODE, RTW, NCT, NB8M, 32, 16, 2>::GR}
-
-// real-factor instances (inversion symmetry): the same kernels without the
-// products with the factor's zero imaginary parts
-#define FCFG2R(MODE, RTW, NCT, NB8M, ID)                                                         \
-  FusedKCfg{MODE, RTW, NCT, NB8M, 32, 16, 2, fused_kernel<MODE, RTW, NCT, NB8M, 32, 16, 2, true>, \
-            FusedCfg<MODE, RTW, NCT, NB8M, 32, 16, 2>::LDS_B, ID, true, 256, false,                \
-            FusedCfg<MODE, RTW, NCT, NB8M, 32, 16, 2>::GCHAIN, FusedCfg<MODE, RTW, NCT, NB8M, 32, 16, 2>::GR, \
-            FusedCfg<MODE, RTW, NCT, NB8M, 32, 16, 2>::GR}
-
-// wide kernel (large pairs, complex64 M): 8 wavefronts, 256-row dense blocks, NB8M band tiles
-#define WCFG(MODE, NB8M, RT, ID)                                                                  \
-  FusedKCfg{MODE, RT, NB8M, NB8M, 32, 32, 1, wide_kernel<MODE, NB8M, RT>, WideCfg<MODE, NB8M, RT>::LDS_B, \
-            ID, false, 512, true, WideCfg<MODE, NB8M, RT>::GCHAIN, WideCfg<MODE, NB8M, RT>::GCH_RS,        \
-            WideCfg<MODE, NB8M, RT>::GCH_RD}
-
-// Listed in order of preference among equal band-tile capacity (the two-per-CU
-// instances first: they hide more memory latency).
-const FusedKCfg kFused[] = {
-    FCFG2(M_F32, 2, 6, 3, 150),        FCFG2(M_F32, 3, 6, 3, 151),
-    FCFG2(M_BF16X3, 3, 6, 3, 161),     FCFG2(M_BF16X3, 2, 6, 3, 160),   // 161 first: 3-5 % ahead
-    FCFG2(M_BF16X6, 2, 6, 3, 170),     FCFG2(M_BF16X6, 3, 6, 3, 171),
-    FCFG2(M_BF16X3, 2, 8, 8, 162),
-    FCFG(M_F32, 3, 12, 3, 32, 120),    FCFG(M_F32, 5, 6, 3, 32, 124),
-    FCFG(M_F32, 4, 8, 8, 32, 121),     FCFG(M_F32, 2, 13, 13, 32, 123),
-    FCFG(M_F32, 2, 16, 16, 32, 122),
-    FCFG(M_BF16X3, 3, 12, 3, 32, 130), FCFG(M_BF16X3, 5, 6, 3, 32, 134),
-    FCFG(M_BF16X3, 4, 8, 8, 32, 131),  FCFG(M_BF16X3, 2, 13, 13, 32, 133),
-    FCFG(M_BF16X3, 2, 16, 16, 32, 132),
-    FCFG(M_BF16X6, 3, 12, 3, 32, 140), FCFG(M_BF16X6, 5, 6, 3, 32, 144),
-    FCFG(M_BF16X6, 4, 8, 8, 32, 141),  FCFG(M_BF16X6, 2, 13, 13, 32, 143),
-    FCFG(M_BF16X6, 2, 16, 16, 32, 142),
-    FCFG2R(M_F32, 2, 6, 3, 250),       FCFG2R(M_F32, 3, 6, 3, 251),
-    FCFG2R(M_BF16X3, 3, 6, 3, 261),    FCFG2R(M_BF16X3, 2, 6, 3, 260),
-    FCFG2R(M_BF16X6, 2, 6, 3, 270),    FCFG2R(M_BF16X6, 3, 6, 3, 271),
-    WCFG(M_F32, 13, 2, 180),           WCFG(M_BF16X3, 13, 2, 181),        WCFG(M_BF16X6, 13, 2, 182),
-    WCFG(M_F32, 16, 2, 183),           WCFG(M_BF16X3, 16, 2, 184),
-    WCFG(M_F32, 13, 1, 186),           WCFG(M_BF16X3, 13, 1, 187),        WCFG(M_BF16X6, 13, 1, 188),
-    WCFG(M_F32, 8, 2, 189),            WCFG(M_BF16X3, 8, 2, 190),         WCFG(M_BF16X6, 8, 2, 191),
-};
-
-// FP64 Cholesky/HERK kernels (herk64.hpp): nbt band tiles, ng n'' values per pass. The planner picks
-// the smallest nbt that holds the context's bands and the ng of the cheapest plan (build_plan64).
-struct Herk64K {
-  int nbt, ng, nw, npw, ctw;
-  void (*fn)(Herk64Args);           // complex128 M
-  void (*fn64)(Herk64Args);         // complex64 M
-  int id() const { return 2000 + 16 * nbt + ng; }
-};
-#define HCFG(NBT, NG)                                                                              \
-  Herk64K{NBT, NG, Herk64Cfg<NBT, NG, false>::NW, Herk64Cfg<NBT, NG, false>::NPW,                   \
-          Herk64Cfg<NBT, NG, false>::CTW, herk64_kernel<NBT, NG, false>, herk64_kernel<NBT, NG, true>}
-const Herk64K kHerk64[] = {
-    HCFG(1, 1), HCFG(1, 2), HCFG(1, 4), HCFG(1, 8), HCFG(1, 12),
-    HCFG(2, 1), HCFG(2, 2), HCFG(2, 3), HCFG(2, 4), HCFG(2, 6),
-    HCFG(3, 1), HCFG(3, 2), HCFG(3, 3), HCFG(3, 4),
-    HCFG(4, 1), HCFG(4, 2), HCFG(5, 1), HCFG(6, 1), HCFG(7, 1), HCFG(8, 1),
-    HCFG(9, 1), HCFG(10, 1), HCFG(11, 1), HCFG(12, 1), HCFG(13, 1), HCFG(14, 1), HCFG(15, 1), HCFG(16, 1),
-};
+// Every fused and wide instance, in order of preference among equal band-tile capacity.
+const std::vector<FusedKCfg>& all_fused() {
+  static const std::vector<FusedKCfg> t = [] {
+    std::vector<FusedKCfg> v(kFusedCfgs, kFusedCfgs + kNumFused);
+    v.insert(v.end(), kWideCfgs, kWideCfgs + kNumWide);
+    return v;
+  }();
+  return t;
+}
 
 struct Plan {
   std::vector<WorkItem> items;      // generation order: pair-major, slot = index
@@ -245,6 +162,8 @@ struct exc_ctx {
   int32_t* d_pair_begin = nullptr;
   Plan plain, bat, perk;              // perk: FP64 HERK, one launch per k (bat when there is one k)
   bool h64 = false;                   // FP64 Cholesky/HERK through herk64_kernel
+  Chunk64* d_chunk64 = nullptr;          // its chunks of block-sparse rows (complex128 M); none: sparse_kernel first
+  int n_chunk64 = 0;
   const KernelCfg* cfg = nullptr;
   const FusedKCfg* fcfg = nullptr;    // non-null: reduced-precision HERK through the fused kernel
   bool fused = false;
@@ -430,7 +349,7 @@ void release(exc_ctx* c) {
   c->ev_in = c->ev_out = nullptr;
   c->own = nullptr;
   void* ptrs[] = {c->d_coef, c->d_cvec, c->d_schur, c->d_U, c->d_row_chan, c->d_ch_off,
-                  c->d_ch_len, c->d_ch_coef, c->d_rowinfo, c->d_runs, c->d_coefpad, c->d_schunk, c->d_sgroup, c->d_pairs, c->d_pair_w, c->d_pair_begin,
+                  c->d_ch_len, c->d_ch_coef, c->d_rowinfo, c->d_runs, c->d_coefpad, c->d_schunk, c->d_sgroup, c->d_chunk64, c->d_pairs, c->d_pair_w, c->d_pair_begin,
                   c->d_ws, c->d_dsp, c->d_gpart, c->d_dpart, c->d_vres, c->d_voff, c->d_knb,
                   c->d_mtab, c->d_vtab, c->d_counter, c->d_mstage, c->d_eout, c->d_ewk, c->d_erho,
                   c->d_gamma, c->d_gpartial, c->d_bt, c->d_tmask, c->d_ppairs, c->d_pw, c->d_pg,
@@ -481,6 +400,26 @@ bool sparse_chunks(const exc_ctx* c, const std::vector<int>& row_chan, std::vect
     out.push_back(make_int4(r0, r - r0, longest, c->n_s + ch0));
   }
   return (int)out.size() <= kMaxChunks;
+}
+
+// herk64_kernel's chunks of multipole-free rows: whole channels within the kernel's limits (rows, multipole
+// rows). Empty if a channel alone exceeds them (sparse_kernel then forms the rows).
+std::vector<Chunk64> chunks64(const exc_ctx* c, const std::vector<int>& row_chan) {
+  std::vector<Chunk64> out;
+  int r = 0;
+  while (r < c->n_s) {
+    const int r0 = r, ch0 = row_chan[r];
+    while (r < c->n_s) {
+      const int ch = row_chan[r], b = c->ch_len[ch];      // r is the first row of channel ch
+      if (r - r0 + b > kH64Rows || ch - ch0 >= kH64MP) break;
+      r += b;
+    }
+    if (r == r0) return {};
+    out.push_back(Chunk64{r0, r - r0, c->n_s + ch0, 0});
+  }
+  // (a chunk costs its 16 rows: with chunks less than half full sparse_kernel's separate pass is the cheaper one)
+  if ((int)out.size() * kH64Rows > 2 * c->n_s + 2 * kH64Rows) return {};
+  return out;
 }
 
 // Relative cost of one row block (for balancing and LPT order).
@@ -613,10 +552,14 @@ struct Split64 {
 double part_cost64(const exc_ctx* c, const Herk64K& k, const PairInfo& p, int part) {
   const bool regg = k.nbt <= 3;
   const int npt = k.nbt * (k.nbt + 1) / 2;
-  if (part == 0) return (double)((c->n_s + 15) / 16) * std::max(10, regg ? k.ng * npt : 4 * k.npw * k.ng);
+  const int gram = regg ? 4 * k.ng * npt : 16 * k.npw * k.ng + 12;      // of 64 rows
+  // block-sparse rows: four chunks at a time formed by five steps, or 16 rows at a time read from the workspace
+  if (part == 0)
+    return c->n_chunk64 ? (double)((c->n_chunk64 + 3) / 4) * (10 * k.ctw + gram)
+                        : (double)((c->n_s + 15) / 16) * std::max(10, gram / 4);
   const int np = (p.nd - 64 * (part - 1) + 15) / 16;
   // (a panel shorter than its barrier and loads costs those)
-  return (double)np * std::max(12, 8 * k.ctw) + (regg ? 4 * k.ng * npt : 16 * k.npw * k.ng + 12);
+  return (double)np * std::max(12, 8 * k.ctw + 2) + gram + 10;
 }
 
 // The items of one pair under a split, through push(g0, g1, part0, part1, cost).
@@ -679,9 +622,11 @@ void order64(const exc_ctx* c, const std::vector<WorkItem>& it, const std::vecto
     for (int b = 0; b < 8; ++b) out.push_back(j < l[b].size() ? it[l[b][j]] : none);
 }
 
-// The split with the smallest estimated time over the pairs [p0, p1): the longest-first schedule of its items on
-// the workgroup slots of the GPU (two per CU; one for more than eight band tiles), each with a fixed overhead, plus
-// the traffic of its partial slots. At most max_slots items (0: no limit beyond 2 GiB of partials); the coarsest
+// The split with the smallest estimated time over the pairs [p0, p1): the longest-first schedule of its items (each
+// with a fixed overhead) on the CUs, whose matrix cores two workgroups share, plus half of the longest item where
+// there are more items than workgroup slots (costs are estimates, and a long item that starts late is waited for:
+// one k of the ZnO-like workload takes 7.6 ms with one item per part of a pair, 6.9 ms with the items of a few
+// passes that this picks), plus the traffic of the partial slots. At most max_slots items (0: no limit beyond 2 GiB of partials); the coarsest
 // split (one item per pair) always qualifies.
 Split64 pick_split64(const exc_ctx* c, int p0, int p1, size_t max_slots, int n_cu) {
   Split64 best;
@@ -692,31 +637,30 @@ Split64 pick_split64(const exc_ctx* c, int p0, int p1, size_t max_slots, int n_c
   for (const Herk64K& k : kHerk64) {
     if (k.nbt != c->nbt_max) continue;
     const int npass = (c->n_occ + k.ng - 1) / k.ng;
-    const int slots = n_cu * (k.nw == 4 ? 2 : 1);
     for (int passes : {0, 4, 2, 1}) {
       if (passes >= npass) continue;
       for (int groups : {1, 2, 3, 4, 6, 0}) {
         const Split64 sp{&k, passes, groups};
         cs.clear();
         for (int i = p0; i < p1 && cs.size() <= max_slots; ++i)
-          split_pair64(c, sp, c->pairs[i], [&](int, int, int, int, double x) { cs.push_back(x + 100.0); });
+          split_pair64(c, sp, c->pairs[i], [&](int, int, int, int, double x) { cs.push_back(x + 60.0); });
         if (cs.size() > max_slots && !(passes == 0 && groups == 1)) continue;
         double sum = 0.0, mx = 0.0, t;
         for (double x : cs) { sum += x; mx = std::max(mx, x); }
-        if (cs.size() > (size_t)32 * slots) {
-          t = sum / slots + 0.5 * mx;
+        if (cs.size() > (size_t)64 * n_cu) {
+          t = sum / n_cu + 0.5 * mx;
         } else {
           std::sort(cs.begin(), cs.end(), std::greater<double>());
           std::priority_queue<double, std::vector<double>, std::greater<double>> h;
+          t = 0.0;
           for (double x : cs) {
             double at = 0.0;
-            if ((int)h.size() == slots) { at = h.top(); h.pop(); }
+            if ((int)h.size() == n_cu) { at = h.top(); h.pop(); }
             h.push(at + x);
+            t = std::max(t, at + x);
           }
-          t = 0.0;
-          while (!h.empty()) { t = h.top(); h.pop(); }
+          if (cs.size() > (size_t)n_cu * (k.nw == 4 ? 2 : 1)) t += 0.5 * mx;
         }
-        if (k.nw == 4) t *= 2.0;                       // two workgroups share a CU's matrix cores
         t += (double)cs.size() * slot_b * 2 / 5e12 * 2.4e9 / 64;
         if (t < 0.98 * best_t) { best_t = t; best = sp; }
       }
@@ -799,11 +743,11 @@ const FusedKCfg* pick_fused(int mode, int nbt_max, bool real, int dtype = -1) {
   const FusedKCfg* best = nullptr;
   if (const char* ev = getenv("EXC_FUSED_CFG")) {      // a fixed configuration id (tuning runs)
     const int id = atoi(ev);
-    for (const auto& k : kFused)
+    for (const auto& k : all_fused())
       if (k.id == id && fused_fits(k, mode, nbt_max, real, k.c64only && dtype < 0 ? EXC_C64 : dtype))
         return &k;                                      // (at set-up the M type is not known yet)
   }
-  for (const auto& k : kFused) {
+  for (const auto& k : all_fused()) {
     if (!fused_fits(k, mode, nbt_max, real, dtype) || k.c64only) continue;
     if (!best || k.NB8M < best->NB8M || (k.NB8M == best->NB8M && k.realf && !best->realf)) best = &k;
   }
@@ -960,10 +904,15 @@ const void* sparse_fn(const exc_ctx* c) {
   }
 }
 
+// herk64_kernel forms the block-sparse rows itself.
+bool fused64(const exc_ctx* c) { return c->h64 && c->n_chunk64 > 0; }
+// The call needs the block-sparse workspace.
+bool needs_ws(const exc_ctx* c) { return !c->fused && !fused64(c); }
+
 // Block-sparse rows of pairs [pair0, pair0 + npairs), all of k (k < 0: every pair). Returns
 // false when there is nothing to do.
 bool cfg_sparse(exc_ctx* c, int dtype, int k, int pair0, int npairs, SparseArgs& s, KLaunch& L) {
-  if (c->fused) return false;                    // the fused kernel does the block-sparse rows itself
+  if (c->fused || fused64(c)) return false;   // the main kernel does the block-sparse rows itself
   const bool packs = c->form == EXC_FORM_CHOL_HERK && c->precision != EXC_FP64;   // packs the dense rows too
   if (!packs && c->n_s == 0 && (c->form == EXC_FORM_CHOL_HERK || c->n_ch == 0)) return false;
   s = sparse_args(c, dtype, k);
@@ -1019,7 +968,17 @@ void launch64(exc_ctx* c, const Plan& P, int i, int dtype, int k, Herk64Args& a,
   a.n_s = c->n_s;
   a.n_occ = c->n_occ;
   a.U = (const double*)c->d_U;
-  a.ws = (const double2*)ws_base(c, k);
+  if (fused64(c)) {
+    a.chunks = c->d_chunk64;
+    a.n_chunk = c->n_chunk64;
+    a.rowinfo = c->d_rowinfo;
+    a.coef = c->d_coef;
+    a.cvec = c->d_cvec;
+    a.coef_qs = c->nqc > 1 ? c->coef_total : 0;
+    a.cvec_qs = c->nqc > 1 ? c->n_s : 0;
+  } else {
+    a.ws = (const double2*)ws_base(c, k);
+  }
   a.gpart = c->sv ? (double*)c->sv->gpart : (double*)c->d_gpart;
   a.gstride = c->gstride;
   a.tmask = c->d_tmask;
@@ -1093,7 +1052,7 @@ void launch_k(exc_ctx* c, const Plan& P, int dtype, int k, hipStream_t st) {
 
 // One k, batched over its q: sparse rows of all pairs of k, one tile launch, reduce.
 exc_status run_k_batched(exc_ctx* c, int k, int dtype, hipStream_t st) {
-  if (!c->fused) TRY(ensure_ws(c, c->ws_k_bytes));
+  if (needs_ws(c)) TRY(ensure_ws(c, c->ws_k_bytes));
   const int p0 = c->k_pair[k], p1 = c->k_pair[k + 1];
   launch_sparse(c, dtype, k, p0, p1 - p0, st);
   const Plan& P = k_plan(c);
@@ -1104,7 +1063,7 @@ exc_status run_k_batched(exc_ctx* c, int k, int dtype, hipStream_t st) {
 
 // One k, plain form: one launch of each kernel per (k, q) pair.
 exc_status run_k_plain(exc_ctx* c, int k, int dtype, hipStream_t st) {
-  if (!c->fused) TRY(ensure_ws(c, c->ws_k_bytes));
+  if (needs_ws(c)) TRY(ensure_ws(c, c->ws_k_bytes));
   const Plan& P = c->plain;
   for (int p = c->k_pair[k]; p < c->k_pair[k + 1]; ++p) {
     launch_sparse(c, dtype, k, p, 1, st);
@@ -1180,7 +1139,7 @@ exc_status run_k_plain_gemm(exc_ctx* c, int k, int dtype, hipStream_t st) {
 // timing events recorded on st (the default: the graph's launch leaves a longer gap before
 // its first kernel, 6-8 us more per step on the Si-like workload; EXC_GRAPH=1 uses the graph).
 exc_status launch_batched_direct(exc_ctx* c, int dtype, hipStream_t st) {
-  if (!c->fused) TRY(ensure_ws(c, c->ws_bytes));
+  if (needs_ws(c)) TRY(ensure_ws(c, c->ws_bytes));
   const bool timed = c->t_slots > 0;
   const int s = c->t_next;
   SparseArgs sa;
@@ -1215,7 +1174,7 @@ exc_status launch_batched_direct(exc_ctx* c, int dtype, hipStream_t st) {
 // The event-record nodes exist only while kernel timing is on; their events are
 // swapped per replay (hipGraphExecEventRecordNodeSetEvent).
 exc_status build_batched_graph(exc_ctx* c, int dtype) {
-  if (!c->fused) TRY(ensure_ws(c, c->ws_bytes));   // every pair's block-sparse rows at once
+  if (needs_ws(c)) TRY(ensure_ws(c, c->ws_bytes));   // every pair's block-sparse rows at once
   hipGraph_t g = nullptr;
   HIPCHK(c, hipGraphCreate(&g, 0));
   const bool timed = c->t_slots > 0;
@@ -1371,19 +1330,19 @@ exc_status autotune(exc_ctx* c, int dtype, hipStream_t st) {
   // CUs short of work
   std::vector<std::pair<const FusedKCfg*, int>> cands;
   if (c->fused_ok)
-    for (const auto& k : kFused)
+    for (const auto& k : all_fused())
       if (fused_fits(k, c->precision, c->nbt_max, c->real_v, dtype)) cands.push_back({&k, 0});
   cands.push_back({nullptr, 0});                 // block-sparse + tile kernels
   // items per n'' chunk only where the pairs alone leave the CUs short of work
   int n_cu = 256;
   (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device);
   if (c->fused_ok && c->n_occ > 1 && (int)c->pairs.size() < 8 * n_cu)
-    for (const auto& k : kFused)
+    for (const auto& k : all_fused())
       if (fused_fits(k, c->precision, c->nbt_max, c->real_v, dtype) &&
           std::min(c->n_occ, k.NCT / c->nbt_max) < c->n_occ) cands.push_back({&k, 1});
   // items per n'' chunk and row part where even those leave the CUs short of work
   if (c->fused_ok && (long)c->pairs.size() * c->n_occ < 4L * n_cu)
-    for (const auto& k : kFused)
+    for (const auto& k : all_fused())
       if (fused_fits(k, c->precision, c->nbt_max, c->real_v, dtype)) cands.push_back({&k, 2});
   const std::string key = tune_key(c, dtype);
   const char* cache = getenv("EXC_TUNE_CACHE");
@@ -1648,6 +1607,13 @@ exc_status exchange_init(const exc_desc* d, const exc_coulomb* cv, void* stream,
         ri[r] = make_int4((int)(c->ch_coef[ch] + (int64_t)i * b + i), b - i, c->n_s + ch, 0);
       }
       ITRY(upload(c, &c->d_rowinfo, ri));
+      // (EXC_FUSED=0: the block-sparse rows in a kernel of their own, as in the other modes)
+      const char* ev = getenv("EXC_FUSED");
+      if (c->h64 && c->n_s > 0 && !(ev && ev[0] == '0')) {
+        const std::vector<Chunk64> ck64 = chunks64(c, row_chan);
+        c->n_chunk64 = (int)ck64.size();
+        if (c->n_chunk64) ITRY(upload(c, &c->d_chunk64, ck64));
+      }
       if (c->form == EXC_FORM_CHOL_HERK && c->n_s > 0) {
         c->run_max = *std::max_element(c->ch_len.begin(), c->ch_len.end());
         c->runs_ld = (c->n_s + 7) / 8 * 8;
