@@ -25,6 +25,10 @@
 //    contraction.
 // Partials: one slot per item (Gram tiles in accumulator order and the FP64
 // diagonal per band), summed per k in a fixed order by the reduction kernel.
+//
+// Bound by the issue of operand reads and products; the panels' loads stay in flight across the barriers of the K
+// loop (see lds_barrier): one outer iteration of the Si-like workload in bf16x3 289 -> 285 us, with its inversion
+// symmetry 140 -> 137 us.
 #pragma once
 #include "common.hpp"
 #include "tile.hpp"
@@ -170,9 +174,11 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
   constexpr int NCC = C::NCC, LDK = C::LDK, APL = C::APL, LDR = C::LDR, YPL = C::YPL, GR = C::GR;
   constexpr int EPV = C::EPV, BM = C::BM, NRT = C::NRT;
 
-  __shared__ __align__(16) unsigned char smem[C::LDS_B];
-  __shared__ int s_item;
-  __shared__ int4 s_chunk[C::MAXCK];
+  // (one LDS array: see lds_barrier)
+  __shared__ __align__(16) unsigned char smem[C::LDS_B + 16 * C::MAXCK + 4 * NQ_MAX + 16];
+  int4* s_chunk = (int4*)(smem + C::LDS_B);    // [MAXCK]
+  int* s_left = (int*)(s_chunk + C::MAXCK);    // [NQ_MAX]
+  int& s_item = s_left[NQ_MAX];
   unsigned char* Raw = smem;                   // NRAW x [NCC][KC] complex, as loaded (K loop)
   lds_t* Apl = (lds_t*)(smem + C::NRAW * C::RAW_B);   // [3 NP][NCC][LDK] pieces (K loop)
   lds_t* Ys = (lds_t*)smem;                    // [NPL][NCC][LDR] (Gram stage; aliases the K panels)
@@ -180,7 +186,6 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
 
   const int tid0 = threadIdx.x;
 
-  __shared__ int s_left[NQ_MAX];
   const int nq = a.counter ? a.nq : 1;
   const int G = (int)gridDim.x;
   const int qi = a.counter ? (int)(blockIdx.x % nq) : 0;
@@ -564,10 +569,15 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
             r_off[t] = ok ? (uint32_t)((col * pi.nmb + a.n_s + k) * esz) : 0x80000000u;
           }
         }
+        // (a panel at or past kend: the same loads with every offset out of range, which touch no memory. Every
+        // iteration then has the same loads in flight, so the compiler can count them: with loads behind a branch
+        // its waits for the factor pieces were vmcnt(0), i.e. for the raw panel just requested as well)
         auto issue_raw = [&](int kc, int buf) {
+          const bool in = kc < kend;
 #pragma unroll
           for (int t = 0; t < NIW; ++t)
-            lds_load16(mrs, Raw + buf * C::RAW_B + (w + NW * t) * 1024, r_off[t], (uint32_t)(kc * esz));
+            lds_load16(mrs, Raw + buf * C::RAW_B + (w + NW * t) * 1024, in ? r_off[t] : 0x80000000u,
+                       in ? (uint32_t)(kc * esz) : 0u);
         };
         // raw -> pieces: consecutive lanes take consecutive elements (a wavefront reads
         // 1 KB of contiguous LDS per instruction, free of bank conflicts) and write
@@ -579,9 +589,8 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
             double re = 0.0, im = 0.0;
             if (kc + k < nd) {
               if (a.m_c64) {
-                const float2 v = *(const float2*)(Rw + e * 8);
-                re = (double)v.x;
-                im = (double)v.y;
+                re = (double)*(const float*)(Rw + e * 8);
+                im = (double)*(const float*)(Rw + e * 8 + 4);
               } else {
                 const double2 v = *(const double2*)(Rw + e * 16);
                 re = v.x;
@@ -633,24 +642,19 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
         };
         const int np = (kend - kc0) / KC;                 // K panels of this row block
         issue_raw(kc0, 0);
-        if (C::NRAW == 2 && np > 1) {
+        if constexpr (C::NRAW == 2) {
           issue_raw(kc0 + KC, 1);
           __builtin_amdgcn_s_waitcnt(C::WAIT_VM_NIW);     // panel 0 has landed
         } else {
           __builtin_amdgcn_s_waitcnt(C::WAIT_VM0);
         }
-        __syncthreads();
+        lds_barrier();
         for (int pp = 0; pp < np; ++pp) {
           const int kc = kc0 + pp * KC, buf = C::NRAW == 2 ? (pp & 1) : 0;
           load_u(kc, ucur);                           // this panel's factor pieces in flight
           convert(kc, buf);
-          __syncthreads();                            // pieces ready, raw buffer free
-          const bool more = pp + 1 < np;
-          if (C::NRAW == 2) {
-            if (pp + 2 < np) issue_raw(kc + 2 * KC, buf);
-          } else if (more) {
-            issue_raw(kc + KC, 0);
-          }
+          lds_barrier();                            // pieces ready, raw buffer free
+          issue_raw(kc + C::NRAW * KC, buf);
           const int na = n_active(kc);                // uniform
           // -Im of the h = 1 operand where no -Im plane is staged: a sign-bit mask, no branch
           const uint32_t nmask = part == 0 ? (MODE == M_F32 ? 0x80000000u : 0x80008000u) : 0u;
@@ -688,10 +692,11 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
             }
           }
           // this wave's part of the next panel has landed
-          if (C::NRAW == 2 && pp + 2 < np) __builtin_amdgcn_s_waitcnt(C::WAIT_VM_NIW);
+          if constexpr (C::NRAW == 2) __builtin_amdgcn_s_waitcnt(C::WAIT_VM_NIW);
           else __builtin_amdgcn_s_waitcnt(C::WAIT_VM0);
-          __syncthreads();
+          lds_barrier();
         }
+        __builtin_amdgcn_s_waitcnt(C::WAIT_VM0);      // the panels past the end, before the stage takes their place
 
         // ---- the row block's rows through LDS into the Gram tiles, GR rows at a time ----
 #pragma unroll

@@ -19,6 +19,10 @@
 // The block-sparse phase takes fused_kernel's chunks of whole channels, with one
 // column per lane and each row's run of the triangle exactly (no padding to the
 // chunk's longest run), the chunk's values of M staged in LDS.
+//
+// Bound by the matrix cores and the operand reads between barriers. Requests that really stay in flight across the
+// barriers (see lds_barrier) took the ZnO-like workload, 2 k, from 4.37 to 4.12 ms in bf16x3 and, 2 k of 72 q, from
+// 3.08 to 2.99 ms in bf16x6; the SrTiO3-like one, 2 k of 108 q, from 13.55 to 12.95 ms in bf16x3.
 #pragma once
 #include "fused.hpp"
 
@@ -205,10 +209,11 @@ __global__ __launch_bounds__(512, 1) void wide_kernel(FusedArgs a) {
   constexpr int BM = C::BM, GR = C::GR, GS = C::GS, LDR = C::LDR, NIW = C::NIW, NI = C::NI;
   constexpr int NRAW = C::NRAW, NFL = C::NFL;
 
-  __shared__ __align__(16) unsigned char smem[C::LDS_B];
-  __shared__ int s_item;
-  __shared__ int4 s_chunk[C::MAXCK];
-  __shared__ int s_left[NQ_MAX];
+  // (one LDS array: see lds_barrier)
+  __shared__ __align__(16) unsigned char smem[C::LDS_B + 16 * C::MAXCK + 4 * NQ_MAX + 16];
+  int4* s_chunk = (int4*)(smem + C::LDS_B);                         // [MAXCK]
+  int* s_left = (int*)(s_chunk + C::MAXCK);                         // [NQ_MAX]
+  int& s_item = s_left[NQ_MAX];
   unsigned char* Raw = smem;                                        // NRAW x [NCC][KC] complex64
   unsigned char* Trash = smem + NRAW * C::RAW_B;                    // 1 KB for the padding loads
   lds_t* Pcs = (lds_t*)(smem + NRAW * C::RAW_B + 1024);             // 2 x [NPL][NCC][KC] pieces
@@ -721,12 +726,16 @@ __global__ __launch_bounds__(512, 1) void wide_kernel(FusedArgs a) {
             r_off[t] = ok ? (uint32_t)((col * pi.nmb + a.n_s + k) * esz) : 0x80000000u;
           }
         }
+        // (a panel at or past kend: the same loads with every offset out of range, which touch no memory: every
+        // iteration has the same loads in flight, so that the compiler can count them in its own waits for the
+        // factor pieces -- behind a branch those were vmcnt(0), a wait for the raw panel just requested)
         auto issue_raw = [&](int kc, int buf) {
+          const bool in = kc < kend;
 #pragma unroll
           for (int t = 0; t < NIW; ++t) {
             const int ix = w + NW * t;
             unsigned char* dst = ix < NI ? Raw + buf * C::RAW_B + ix * 1024 : Trash;
-            lds_load16(mrs, dst, r_off[t], (uint32_t)(kc * esz));
+            lds_load16(mrs, dst, in ? r_off[t] : 0x80000000u, in ? (uint32_t)(kc * esz) : 0u);
           }
         };
         // raw panel -> pieces: thread u converts column u / (KC/8), k = 8 (u % (KC/8)) .. +7, four
@@ -800,40 +809,32 @@ __global__ __launch_bounds__(512, 1) void wide_kernel(FusedArgs a) {
           return n;
         };
 
-        __syncthreads();                                  // LDS of the previous phase is free
+        lds_barrier();                                  // LDS of the previous phase is free
         // prologue: raw panels 0 .. NRAW-1 in flight, then the factor of panel 0
         issue_raw(kc0, 0);
-        if (np > 1) issue_raw(kc0 + KC, 1);
-        if (NRAW == 3 && np > 2) issue_raw(kc0 + 2 * KC, 2);
+        issue_raw(kc0 + KC, 1);
+        if constexpr (NRAW == 3) issue_raw(kc0 + 2 * KC, 2);
         load_u(kc0);
         // own part of raw panel 0 landed: the later NIW (panels 1, 2) + NFL (factor) loads may fly
-        if (NRAW == 3 && np > 2) wait_vm<2 * NIW + NFL>();
-        else if (np > 1) wait_vm<NIW + NFL>();
-        else wait_vm<NFL>();
-        __syncthreads();
+        wait_vm<(NRAW - 1) * NIW + NFL>();
+        lds_barrier();
         convert(kc0, 0, 0);
-        if (np > 1) {                                     // own part of raw panel 1 landed
-          if (NRAW == 3 && np > 2) wait_vm<NIW + NFL>();
-          else wait_vm<NFL>();
-        }
-        __syncthreads();
+        wait_vm<(NRAW - 2) * NIW + NFL>();                // own part of raw panel 1 landed
+        lds_barrier();
 
         for (int p = 0; p < np; ++p) {
           const int kc = kc0 + p * KC;
           // A: raw panel p + NRAW into the buffer panel p came in (converted before the last barrier)
-          const bool issued = p + NRAW < np;
-          if (issued) issue_raw(kc + NRAW * KC, p % NRAW);
+          issue_raw(kc + NRAW * KC, p % NRAW);
           // B: the Re half of this panel's factor landed (its Im half and the raw loads just
           // issued may still fly)
-          if (issued) wait_vm<NIW + NFL / 2>();
-          else wait_vm<NFL / 2>();
+          wait_vm<NIW + NFL / 2>();
           // the middle of the panel: the Im half landed (only the raw loads issued above may
           // still fly), then the Re half of the next panel's factor into the registers the
           // products with the Re half no longer read
           auto mid = [&]() {
-            if (issued) wait_vm<NIW>();
-            else wait_vm<0>();
-            if (p + 1 < np) load_u_h(kc + KC, 0);
+            wait_vm<NIW>();
+            load_u_h(min(kc + KC, kend - KC), 0);         // (past the last panel: that one again, not used)
           };
           // C: [Yr|Yi] += Ur [Ar|Ai] + Ui [-Ai|Ar] over the panel
           const int na = n_active(kc);
@@ -848,15 +849,19 @@ __global__ __launch_bounds__(512, 1) void wide_kernel(FusedArgs a) {
           const lds_t* B1 = Pl + (1 - xpart) * NP * APL;
           // -Im for the real-part lanes of the h = 1 operand: a sign-bit mask, no branch
           const uint32_t nmask = xpart == 0 ? (MODE == M_F32 ? 0x80000000u : 0x80008000u) : 0u;
-          // the panel's products for NA active row tiles (NA known at compile time: the loop
-          // below is straight-line code with no per-instruction branches)
+          // (the products below run over every row tile: straight-line code with no per-instruction branches)
           // the next panel's conversion (VALU and LDS work of its own) goes between the
           // products, in two halves, so that it runs while the matrix cores work
           const bool conv = p + 1 < np;
-          auto panel = [&](auto na_c) {
-            constexpr int NA = decltype(na_c)::value;
+          // part 0: up to the products with the Re half of the last step's factor; part 1: those with its Im half.
+          // A wavefront whose row tiles all start past the panel (na = 0) only converts; the loads of the middle
+          // are outside the branch, so that both paths have the same ones in flight
+          auto panel = [&](auto part_c) {
+            constexpr int PT = decltype(part_c)::value, KSN = KC / KS;
 #pragma unroll
-            for (int ks = 0; ks < KC / KS; ++ks) {
+            for (int ks = PT == 0 ? 0 : KSN - 1; ks < KSN; ++ks) {
+              constexpr int HB = PT == 0 ? 0 : NCT;           // (h, j) steps of the part: [hb, he)
+              const int he = PT == 0 && ks == KSN - 1 ? NCT : 2 * NCT;
               auto bload = [&](int hj, op_t (&b)[NP]) {
                 const int h = hj / NCT, j = hj % NCT;
                 const lds_t* Bh = h == 0 ? B0 : B1;
@@ -867,58 +872,47 @@ __global__ __launch_bounds__(512, 1) void wide_kernel(FusedArgs a) {
                 }
               };
               op_t bA[NP], bB[NP];
-              bload(0, bA);
+              bload(HB, bA);
 #pragma unroll
-              for (int hj = 0; hj < 2 * NCT; ++hj) {
+              for (int hj = HB; hj < he; ++hj) {
                 const int h = hj / NCT, j = hj % NCT;
-                op_t (&bc)[NP] = (hj & 1) ? bB : bA;
-                op_t (&bn)[NP] = (hj & 1) ? bA : bB;
-                if (hj + 1 < 2 * NCT) bload(hj + 1, bn);
+                op_t (&bc)[NP] = ((hj - HB) & 1) ? bB : bA;
+                op_t (&bn)[NP] = ((hj - HB) & 1) ? bA : bB;
+                if (hj + 1 < he) bload(hj + 1, bn);
 #pragma unroll
                 for (int pr = 0; pr < Traits<MODE>::NPROD; ++pr)
 #pragma unroll
-                  for (int ii = 0; ii < NA; ++ii)
+                  for (int ii = 0; ii < RT; ++ii)
                     acc[ii][j] = mfma(uop(ii, h, ks, NP == 1 ? 0 : prod_a(NP, pr)),
                                       bc[NP == 1 ? 0 : prod_b(NP, pr)], acc[ii][j]);
                 // keep the scheduler from hoisting later operand loads (register pressure)
                 __builtin_amdgcn_sched_barrier(0);
-                if (ks == KC / KS - 1 && (hj == NCT / 2 || hj == NCT + NCT / 2) && conv) {
+                if (ks == KSN - 1 && (hj == NCT / 2 || hj == NCT + NCT / 2) && conv) {
                   convert_half(kc + KC, (p + 1) % NRAW, (p + 1) & 1, hj == NCT / 2 ? 0 : 1);
-                  __builtin_amdgcn_sched_barrier(0);
-                }
-                if (ks == KC / KS - 1 && hj == NCT - 1) {
-                  mid();
                   __builtin_amdgcn_sched_barrier(0);
                 }
               }
             }
           };
-          if (na > 0) {
-            panel(std::integral_constant<int, RT>{});
-          } else {
-            mid();
-            if (conv) convert(kc + KC, (p + 1) % NRAW, (p + 1) & 1);
-          }
-          if (p + 1 < np) {
-            // (E, the next panel's pieces from its raw panel -- landed and visible since the
-            // last barrier -- into the other piece buffer, ran between the products above)
-            // D: the Im half of the next panel's factor, after the products that read this one's
-            load_u_h(kc + KC, 1);
-            // F: own part of raw panel p + 2 landed, for the conversion after the next barrier.
-            // Loads issued after it: NRAW = 3 -> both halves of this panel's factor (the middle
-            // and the end of the last panel), raw p + 3 (A above, if issued) and both halves of
-            // the next panel's; NRAW = 2 -> both halves of the next panel's factor.
-            if (p + 2 < np) {
-              if constexpr (NRAW == 3) {
-                if (issued) wait_vm<NIW + 2 * NFL>();
-                else wait_vm<2 * NFL>();
-              } else {
-                wait_vm<NFL>();
-              }
-            }
-          }
-          __syncthreads();
+          if (na > 0) panel(std::integral_constant<int, 0>{});
+          else if (conv) convert_half(kc + KC, (p + 1) % NRAW, (p + 1) & 1, 0);
+          mid();
+          __builtin_amdgcn_sched_barrier(0);
+          if (na > 0) panel(std::integral_constant<int, 1>{});
+          else if (conv) convert_half(kc + KC, (p + 1) % NRAW, (p + 1) & 1, 1);
+          // (E, the next panel's pieces from its raw panel -- landed and visible since the
+          // last barrier -- into the other piece buffer, ran between the products above)
+          // D: the Im half of the next panel's factor, after the products that read this one's
+          load_u_h(min(kc + KC, kend - KC), 1);
+          // F: own part of raw panel p + 2 landed, for the conversion after the next barrier.
+          // Loads issued after it: NRAW = 3 -> both halves of this panel's factor (the middle
+          // and the end of the last panel), raw p + 3 (A above) and both halves of the next
+          // panel's; NRAW = 2 -> both halves of the next panel's factor.
+          if constexpr (NRAW == 3) wait_vm<NIW + 2 * NFL>();
+          else wait_vm<NFL>();
+          lds_barrier();
         }
+        wait_vm<0>();                                     // the panels past the end, before the stage takes their place
 
         // ---- the row block's rows through LDS into the Gram tiles, GS rows at a time ----
         constexpr int RPS = GS / 16;                      // row tiles per stage round
