@@ -103,6 +103,48 @@ __global__ __launch_bounds__(256) void nn_gemm(GemmArgs g) {
       }
 }
 
+// C[M x N] = A[M x K] B^T (B: N x K row-major, contiguous rows) (+ bias, tanh) for at most 16 rows of A and K a
+// multiple of 256 (the layers of a prediction of a few samples): bound by reading B once. A workgroup
+// takes 64 rows of B, 16 per wavefront, whose 1 KB segments go straight to LDS, every load in flight at once (row
+// pitch 1040 bytes: the 16 rows of an operand read meet distinct banks); nn_gemm moves 16 k of 64 rows at a time
+// between two barriers. The products run in nn_gemm's order (k ascending in one accumulator): the same bits. One
+// sample, 75 600 outputs, K = 256 (77 MB): 43 -> 29 us.
+template <int EPI>
+__global__ __launch_bounds__(256) void nn_gemm_rows(GemmArgs g) {
+  constexpr int KS = 256, PITCH = KS + 4;
+  __shared__ __align__(16) float sB[4][16][PITCH];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, l16 = lane & 15, lq = lane >> 4;
+  const int n0 = blockIdx.x * 64 + 16 * w;
+  if (n0 >= g.N) return;                               // whole wavefronts; no barrier below
+  const int rows = min(16, g.N - n0);
+  const auto rs = make_rsrc(g.B + (long)n0 * g.ldb, (uint32_t)(((long)(rows - 1) * g.ldb + g.K) * 4));
+  f4_t acc = f4_t{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 0; k0 < g.K; k0 += KS) {
+    __builtin_amdgcn_wave_barrier();
+    if (k0 > 0) __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0): the previous segment has been read
+    for (int r = 0; r < 16; ++r)                       // (rows past N read zero)
+      lds_load16(rs, &sB[w][r][0], r < rows ? (uint32_t)lane * 16 : 0xFFFFFFF0u, (uint32_t)(r < rows ? r * g.ldb + k0 : 0) * 4);
+    __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): the segments have landed
+    __builtin_amdgcn_wave_barrier();
+    const float* ap = g.A + (long)min(l16, g.M - 1) * g.lda + k0 + lq;
+#pragma unroll 8
+    for (int k = 0; k < KS; k += 4) {
+      const float a = l16 < g.M ? ap[k] : 0.f;
+      acc = mfma(a, sB[w][l16][k + lq], acc);
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int row = acc_row<M_F32>(lq, e), col = n0 + l16;
+    if (row < g.M && col < g.N) {
+      float v = acc[e];
+      if (EPI == EPI_BIAS) v += g.bias[col];
+      if (EPI == EPI_BIAS_TANH) v = tanhf(v + g.bias[col]);
+      g.C[(long)row * g.ldc + col] = v;
+    }
+  }
+}
+
 // g[j] = sum_i D[i*ld + j], i < n (bias gradients), fixed order.
 __global__ __launch_bounds__(256) void nn_colsum(const float* D, int ld, int n, int ncol, float* g) {
   const int j = blockIdx.x * 256 + threadIdx.x;
@@ -177,17 +219,32 @@ __global__ __launch_bounds__(256) void nn_init_params(float* theta, InitArgs a, 
 // Sketch of dP = P_new - P_old: s_i = sum_j S_ij v_j with S_ij = -1 when the
 // top bit of SplitMix64(seed) output i*D + j is set, else +1; v_j runs over
 // (k', column, row, re/im) of the n_kp complex n_b x n_b matrices. Pass 1: one
-// partial vector per chunk of v; pass 2: fixed-order sum, scaling by
-// 1/(sqrt(m) |v|).
+// partial vector per chunk of v, [m + 1][nchunk] (the last row: sums of squares);
+// pass 2: one workgroup per row sums the chunks in a fixed order and scales by
+// 1/(sqrt(m) |v|) (every workgroup forms |v| itself).
+// Pass 1 is bound by the integer multiplies of the m D signs. Only the top bit of an
+// output is used, so the generator's last xor-shift and the low half of its last product
+// are left out, and its state advances by an addition instead of a product per output:
+// 64 x 1 036 800 signs 61.5 -> 51.3 us. Pass 2 was one workgroup with a serial sum over the
+// chunks per row: 227 -> 4 us (507 chunks).
 // ---------------------------------------------------------------------------
 constexpr int SK_CHUNK = 2048;
 constexpr int SK_MMAX = 128;
+
+// Top bit of SplitMix64 output of the (already advanced) state z.
+__device__ __forceinline__ uint32_t splitmix64_top(uint64_t z) {
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z ^= z >> 27;
+  const uint32_t lo = (uint32_t)z, hi = (uint32_t)(z >> 32);
+  // bits 32..63 of z * 0x94D049BB133111EB
+  return (__umulhi(lo, 0x133111EBu) + lo * 0x94D049BBu + hi * 0x133111EBu) >> 31;
+}
 
 __global__ __launch_bounds__(256) void nn_sketch_partial(const double* Pn, const double* Po, long D,
                                                           int m, uint64_t seed, double* part) {
   __shared__ double v[SK_CHUNK];
   __shared__ double red[256];
-  const long j0 = (long)blockIdx.x * SK_CHUNK;
+  const long j0 = (long)blockIdx.x * SK_CHUNK, nchunk = gridDim.x;
   const int len = (int)min((long)SK_CHUNK, D - j0);
   double sq = 0.0;
   for (int j = threadIdx.x; j < SK_CHUNK; j += 256) {
@@ -202,45 +259,57 @@ __global__ __launch_bounds__(256) void nn_sketch_partial(const double* Pn, const
     if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
-  double* out = part + (long)blockIdx.x * (m + 1);
-  if (threadIdx.x == 0) out[m] = red[0];
+  if (threadIdx.x == 0) part[m * nchunk + blockIdx.x] = red[0];
   // each output row i: 256/m threads (at least one) split the chunk; fixed order
+  constexpr uint64_t GAMMA = 0x9E3779B97F4A7C15ull;
   const int per = max(1, 256 / m);
   for (int base = 0; base < m; base += 256 / per) {
     const int i = base + threadIdx.x / per, sub = threadIdx.x % per;
     double s = 0.0;
-    if (i < m) {
-      const uint64_t row0 = (uint64_t)i * (uint64_t)D + (uint64_t)j0;
+    if (i < m && (int)threadIdx.x < 256 / per * per) {
+      uint64_t z = seed + ((uint64_t)i * (uint64_t)D + (uint64_t)j0 + (uint64_t)sub + 1) * GAMMA;
+      const uint64_t dz = (uint64_t)per * GAMMA;
+#pragma unroll 4
       for (int j = sub; j < len; j += per) {
-        const uint64_t r = splitmix64_at(seed, row0 + (uint64_t)j);
-        s += (r >> 63) ? -v[j] : v[j];
+        const double x = v[j];
+        s += __hiloint2double(__double2hiint(x) ^ (int)(splitmix64_top(z) << 31), __double2loint(x));
+        z += dz;
       }
     }
     __syncthreads();
     red[threadIdx.x] = s;
     __syncthreads();
-    if (i < m && sub == 0) {
+    if (i < m && sub == 0 && (int)threadIdx.x < 256 / per * per) {
       double t = 0.0;
       for (int q = 0; q < per; ++q) t += red[threadIdx.x + q];
-      out[i] = t;
+      part[i * nchunk + blockIdx.x] = t;
     }
   }
 }
 
-__global__ __launch_bounds__(128) void nn_sketch_final(const double* part, int nchunk, int m, float* x,
+__global__ __launch_bounds__(256) void nn_sketch_final(const double* part, int nchunk, int m, float* x,
                                                         double* norm_out) {
-  __shared__ double nrm;
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int b = 0; b < nchunk; ++b) s += part[(long)b * (m + 1) + m];
-    nrm = sqrt(s);
-    *norm_out = nrm;
+  __shared__ double red[2][256];
+  const int i = blockIdx.x, tid = threadIdx.x;
+  double s = 0.0, q = 0.0;
+  for (int b = tid; b < nchunk; b += 256) {
+    s += part[(long)i * nchunk + b];
+    q += part[(long)m * nchunk + b];
   }
+  red[0][tid] = s;
+  red[1][tid] = q;
   __syncthreads();
-  for (int i = threadIdx.x; i < m; i += 128) {
-    double s = 0.0;
-    for (int b = 0; b < nchunk; ++b) s += part[(long)b * (m + 1) + i];
-    x[i] = nrm > 0.0 ? (float)(s / (sqrt((double)m) * nrm)) : 0.f;
+  for (int o = 128; o > 0; o >>= 1) {
+    if (tid < o) {
+      red[0][tid] += red[0][tid + o];
+      red[1][tid] += red[1][tid + o];
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    const double nrm = sqrt(red[1][0]);
+    x[i] = nrm > 0.0 ? (float)(red[0][0] / (sqrt((double)m) * nrm)) : 0.f;
+    if (i == 0) *norm_out = nrm;
   }
 }
 
@@ -293,33 +362,45 @@ __global__ __launch_bounds__(256) void nn_project(ProjArgs a) {
   }
 }
 
+// A workgroup takes four columns of V(k), one per wavefront: T[:, c] = H conj(B[c, :]) with lane = row i of H
+// (y staged in LDS, the columns' entries of B read once to LDS), then V0 + scale * B T[:, c] with lane = row r. One
+// workgroup per k left 235 of 256 CUs idle (21 k): 21 k of 60 bands, 60 x 60 blocks 326 -> 18 us.
 __global__ __launch_bounds__(256) void nn_expand(ProjArgs a) {
-  extern __shared__ double2 T[];                      // [n][n_blk]: T = H B^H, stored T[c*nbk + i]
-  const int k = blockIdx.x, n = a.nb[k], nbk = a.n_blk;
+  extern __shared__ float ys[];                       // [n_blk][n_blk + 1], then double2 bc[4][n_blk], T[4][n_blk]
+  const int k = blockIdx.x, n = a.nb[k], nbk = a.n_blk, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int c0 = (int)blockIdx.y * 4;
+  if (c0 >= n) return;                                // uniform
   const double2* B = a.Z + a.z_off[k];
   const float* y = a.y + (long)k * nbk * nbk;
-  for (int e = threadIdx.x; e < n * nbk; e += 256) {
-    const int i = e % nbk, c = e / nbk;
-    double2 s = make_double2(0.0, 0.0);
-    for (int j = 0; j < nbk; ++j) {
-      double2 h;
-      if (i == j) h = make_double2((double)y[i * nbk + i], 0.0);
-      else if (i < j) h = make_double2((double)y[i * nbk + j], (double)y[j * nbk + i]);
-      else h = make_double2((double)y[j * nbk + i], -(double)y[i * nbk + j]);
-      const double2 b = B[c + (long)j * n];
-      s = cfma(h, make_double2(b.x, -b.y), s);       // H_ij conj(B_cj)
+  double2* bc = (double2*)(ys + (nbk * (nbk + 1) + 3) / 4 * 4);
+  double2* T = bc + 4 * nbk;
+  for (int e = threadIdx.x; e < nbk * nbk; e += 256) ys[e / nbk * (nbk + 1) + e % nbk] = y[e];
+  for (int e = threadIdx.x; e < 4 * nbk; e += 256) bc[e] = B[min(c0 + e / nbk, n - 1) + (long)(e % nbk) * n];
+  __syncthreads();
+  const int c = c0 + w;
+  if (c < n) {
+    for (int i = lane; i < nbk; i += 64) {
+      double2 s = make_double2(0.0, 0.0);
+#pragma unroll 4
+      for (int j = 0; j < nbk; ++j) {
+        const float re = ys[min(i, j) * (nbk + 1) + max(i, j)], im = ys[max(i, j) * (nbk + 1) + min(i, j)];
+        const double2 h = make_double2((double)re, i == j ? 0.0 : (i < j ? (double)im : -(double)im));
+        const double2 b = bc[w * nbk + j];
+        s = cfma(h, make_double2(b.x, -b.y), s);      // H_ij conj(B_cj)
+      }
+      T[w * nbk + i] = s;
     }
-    T[c * nbk + i] = s;
   }
   __syncthreads();
-  const double2* V0 = a.Vanc[k];
-  double2* Vo = a.Vout[k];
-  for (long e = threadIdx.x; e < (long)n * n; e += 256) {
-    const int r = (int)(e % n), c = (int)(e / n);
+  if (c >= n) return;
+  const double2* V0 = a.Vanc[k] + (long)c * n;
+  double2* Vo = a.Vout[k] + (long)c * n;
+  for (int r = lane; r < n; r += 64) {
+    const double2 v0 = V0[r];
     double2 s = make_double2(0.0, 0.0);
-    for (int i = 0; i < nbk; ++i) s = cfma(B[r + (long)i * n], T[c * nbk + i], s);
-    const double2 v0 = V0[e];
-    Vo[e] = make_double2(v0.x + a.scale * s.x, v0.y + a.scale * s.y);
+#pragma unroll 8
+    for (int i = 0; i < nbk; ++i) s = cfma(B[r + (long)i * n], T[w * nbk + i], s);
+    Vo[r] = make_double2(v0.x + a.scale * s.x, v0.y + a.scale * s.y);
   }
 }
 

@@ -78,11 +78,23 @@ void gemm(hipStream_t st, const float* A, int lda, const float* B, int ldb, floa
   hipLaunchKernelGGL((nn_gemm<TA, TB, EPI>), grid, dim3(256), 0, st, g);
 }
 
+// One layer: Out[n x O] = epi(In[n x K] W^T + b). Up to 16 samples and K a multiple of 256 (the prediction of a few
+// samples; the layer's rows of W are then 1 KB aligned segments): nn_gemm_rows.
+template <int EPI>
+void layer(hipStream_t st, const float* in, int K, const float* W, const float* b, float* out, int O, int n) {
+  if (n <= 16 && K % 256 == 0) {
+    GemmArgs g{in, W, out, b, nullptr, K, K, O, 0, n, O, K};
+    hipLaunchKernelGGL((nn_gemm_rows<EPI>), dim3((O + 63) / 64), dim3(256), 0, st, g);
+  } else {
+    gemm<false, true, EPI>(st, in, K, W, K, out, O, n, O, K, b);
+  }
+}
+
 void nn_forward(NnState* s, hipStream_t st, const float* X, int n, float* y) {
   const float* th = s->theta;
-  gemm<false, true, EPI_BIAS_TANH>(st, X, s->I, th + s->off[0], s->I, s->h1, s->H, n, s->H, s->I, th + s->off[1]);
-  gemm<false, true, EPI_BIAS_TANH>(st, s->h1, s->H, th + s->off[2], s->H, s->h2, s->H, n, s->H, s->H, th + s->off[3]);
-  gemm<false, true, EPI_BIAS>(st, s->h2, s->H, th + s->off[4], s->H, y, s->O, n, s->O, s->H, th + s->off[5]);
+  layer<EPI_BIAS_TANH>(st, X, s->I, th + s->off[0], th + s->off[1], s->h1, s->H, n);
+  layer<EPI_BIAS_TANH>(st, s->h1, s->H, th + s->off[2], th + s->off[3], s->h2, s->H, n);
+  layer<EPI_BIAS>(st, s->h2, s->H, th + s->off[4], th + s->off[5], y, s->O, n);
 }
 
 // forward, loss and dL/dtheta into s->grad (inputs in s->X, s->T)
@@ -278,12 +290,17 @@ exc_status exchange_nn_predict(exc_ctx* c, const float* X, int32_t n, float* Y_o
   TRY(nn_reserve(c, n));
   hipStream_t st = stream ? (hipStream_t)stream : c->own;
   if (stream) HIPCHK(c, hipStreamSynchronize(c->own));   // a training run may still use the buffers
-  TRY(nn_stage(c, s->X, X, (size_t)n * s->I, on_device, st));
+  if (on_device) {
+    nn_forward(s, st, X, n, Y_out);
+    HIPCHK(c, hipGetLastError());
+    if (!stream) HIPCHK(c, hipStreamSynchronize(st));
+    return EXC_OK;
+  }
+  TRY(nn_stage(c, s->X, X, (size_t)n * s->I, 0, st));
   nn_forward(s, st, s->X, n, s->y);
   HIPCHK(c, hipGetLastError());
-  HIPCHK(c, hipMemcpyAsync(Y_out, s->y, (size_t)n * s->O * sizeof(float),
-                           on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, st));
-  if (!on_device || !stream) HIPCHK(c, hipStreamSynchronize(st));
+  HIPCHK(c, hipMemcpyAsync(Y_out, s->y, (size_t)n * s->O * sizeof(float), hipMemcpyDeviceToHost, st));
+  HIPCHK(c, hipStreamSynchronize(st));
   return EXC_OK;
 }
 
@@ -308,7 +325,7 @@ exc_status exchange_nn_features(exc_ctx* c, const double* P_new, const double* P
   }
   hipLaunchKernelGGL(nn_sketch_partial, dim3((unsigned)nchunk), dim3(256), 0, st, P_new, P_old, (long)n_real, m,
                      seed, l->part);
-  hipLaunchKernelGGL(nn_sketch_final, dim3(1), dim3(128), 0, st, l->part, (int)nchunk, m, x_out, norm_out);
+  hipLaunchKernelGGL(nn_sketch_final, dim3(m), dim3(256), 0, st, l->part, (int)nchunk, m, x_out, norm_out);
   HIPCHK(c, hipGetLastError());
   if (!stream) HIPCHK(c, hipStreamSynchronize(st));
   return EXC_OK;
@@ -372,8 +389,8 @@ exc_status exchange_nn_expand(exc_ctx* c, const void* const* Vanchor_k, const vo
   TRY(put_table(c, (void*)l->tabC, (const void* const*)Vout_k, st));
   ProjArgs a{nullptr, nullptr, (const double2*)Z, l->z_off, c->d_knb, n_blk, scale, const_cast<float*>(y),
              (const double2* const*)l->tabA, (double2* const*)l->tabC};
-  const size_t lds = (size_t)c->nb_max * n_blk * sizeof(double2);
-  hipLaunchKernelGGL(nn_expand, dim3(c->n_k), dim3(256), lds, st, a);
+  const size_t lds = (size_t)((n_blk * (n_blk + 1) + 3) / 4) * 16 + (size_t)8 * n_blk * sizeof(double2);
+  hipLaunchKernelGGL(nn_expand, dim3(c->n_k, (c->nb_max + 3) / 4), dim3(256), lds, st, a);
   HIPCHK(c, hipGetLastError());
   if (!stream) HIPCHK(c, hipStreamSynchronize(st));
   return EXC_OK;
