@@ -529,146 +529,6 @@ __global__ void chan_chol_kernel(int n_ch, const int32_t* ch_off, const int32_t*
 }
 
 // ---------------------------------------------------------------------------
-// Dense Cholesky of the (Schur-updated) block E(q) = L22 L22^H, FP64, one
-// workgroup per q, left-looking with 16-column panels.
-// ---------------------------------------------------------------------------
-struct CholArgs {
-  double2* A;             // per-q matrices (column-major, leading dimension lda)
-  const int64_t* a_off;
-  const int32_t* nd;
-  const int32_t* lda;
-  int32_t n_ch;
-  const double* schur;    // [n_ch] (per q: [n_q][n_ch]) or nullptr
-  int32_t schur_qs;       // n_ch when the channel blocks depend on q, else 0
-  int* info;              // [n_q] first failing pivot (1-based), 0 = ok
-};
-
-// threads per q of the dense Cholesky (one row of the panel update per thread: more rows in
-// flight hide the latency of their loads)
-constexpr int kCholThreads = 512;
-__global__ __launch_bounds__(kCholThreads) void dense_chol_kernel(CholArgs a) {
-  constexpr int NTC = kCholThreads;
-  constexpr int NB = 16, PC = 32;
-  static_assert(PC % 8 == 0, "panel stage: whole groups of eight values");
-  __shared__ double2 Lp[NB][PC + 1];
-  __shared__ double2 Ld[NB][NB + 1];
-  __shared__ int s_fail;
-  const int q = blockIdx.x, tid = threadIdx.x;
-  const int n = a.nd[q], lda = a.lda[q];
-  double2* A = a.A + a.a_off[q];
-  if (tid == 0) s_fail = 0;
-  if (a.schur)
-    for (int c = tid; c < a.n_ch && c < n; c += NTC) A[c + (long)c * lda].x -= a.schur[(long)q * a.schur_qs + c];
-  __syncthreads();
-  for (int jb = 0; jb < n; jb += NB) {
-    const int nbk = min(NB, n - jb);
-    // panel update: A[i][jb+jj] -= sum_{p<jb} A[i][p] conj(A[jb+jj][p]),  i >= jb
-    for (int i0 = jb; i0 < n; i0 += NTC) {
-      const int i = i0 + tid;
-      double2 acc[NB];
-#pragma unroll
-      for (int jj = 0; jj < NB; ++jj) acc[jj] = make_double2(0.0, 0.0);
-      for (int p0 = 0; p0 < jb; p0 += PC) {
-        __syncthreads();
-        for (int e = tid; e < NB * PC; e += NTC) {
-          const int jj = e / PC, pp = e % PC;
-          Lp[jj][pp] = (jj < nbk && p0 + pp < jb) ? A[(jb + jj) + (long)(p0 + pp) * lda] : make_double2(0.0, 0.0);
-        }
-        __syncthreads();
-        if (i < n) {
-          // eight values of the row requested together (past the panel's end: zeros, against the
-          // zero-filled stage), then their products
-          const int pe = min(PC, jb - p0);
-          for (int pp0 = 0; pp0 < pe; pp0 += 8) {
-            double2 xv[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-              xv[u] = pp0 + u < pe ? A[i + (long)(p0 + pp0 + u) * lda] : make_double2(0.0, 0.0);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              const double2 x = xv[u];
-#pragma unroll
-              for (int jj = 0; jj < NB; ++jj) {
-                const double2 y = Lp[jj][pp0 + u];
-                acc[jj].x += x.x * y.x + x.y * y.y;
-                acc[jj].y += x.y * y.x - x.x * y.y;
-              }
-            }
-          }
-        }
-      }
-      if (i < n) {
-#pragma unroll
-        for (int jj = 0; jj < NB; ++jj) {           // (fixed bound: acc stays in registers)
-          if (jj < nbk) {
-            double2* t = &A[i + (long)(jb + jj) * lda];
-            t->x -= acc[jj].x; t->y -= acc[jj].y;
-          }
-        }
-      }
-    }
-    __syncthreads();
-    // factor the diagonal block in LDS
-    for (int e = tid; e < NB * NB; e += NTC) {
-      const int r = e % NB, cc = e / NB;
-      Ld[r][cc] = (r < nbk && cc < nbk) ? A[(jb + r) + (long)(jb + cc) * lda] : make_double2(0.0, 0.0);
-    }
-    __syncthreads();
-    if (tid == 0) {
-      for (int j = 0; j < nbk; ++j) {
-        double d = Ld[j][j].x;
-        for (int p = 0; p < j; ++p) d -= Ld[j][p].x * Ld[j][p].x + Ld[j][p].y * Ld[j][p].y;
-        if (!(d > 0.0)) { if (!s_fail) s_fail = jb + j + 1; d = 1.0; }
-        d = sqrt(d);
-        Ld[j][j] = make_double2(d, 0.0);
-        for (int i = j + 1; i < nbk; ++i) {
-          double2 t = Ld[i][j];
-          for (int p = 0; p < j; ++p) {
-            t.x -= Ld[i][p].x * Ld[j][p].x + Ld[i][p].y * Ld[j][p].y;
-            t.y -= Ld[i][p].y * Ld[j][p].x - Ld[i][p].x * Ld[j][p].y;
-          }
-          Ld[i][j] = make_double2(t.x / d, t.y / d);
-        }
-      }
-    }
-    __syncthreads();
-    for (int e = tid; e < nbk * nbk; e += NTC) {
-      const int r = e % nbk, cc = e / nbk;
-      if (r >= cc) A[(jb + r) + (long)(jb + cc) * lda] = Ld[r][cc];
-    }
-    // rows below: x Ld^H = a  ->  x_j = (a_j - sum_{m<j} x_m conj(Ld[j][m])) / Ld[j][j]
-    for (int i = jb + nbk + tid; i < n; i += NTC) {
-      // an index offset of zero the compiler cannot see through: the block's values are read
-      // from LDS per row instead of being hoisted into (spilled) registers for all rows
-      int zb = 0;
-      asm volatile("" : "+v"(zb));
-      const double2* Lz = &Ld[0][0] + zb;
-      double2 x[NB];
-      for (int j = 0; j < NB; ++j) x[j] = j < nbk ? A[i + (long)(jb + j) * lda] : make_double2(0.0, 0.0);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        if (j < nbk) {
-          double2 t = x[j];
-#pragma unroll
-          for (int m = 0; m < NB; ++m) {
-            if (m < j) {
-              const double2 l = Lz[j * (NB + 1) + m];
-              t.x -= x[m].x * l.x + x[m].y * l.y;
-              t.y -= x[m].y * l.x - x[m].x * l.y;
-            }
-          }
-          const double d = Lz[j * (NB + 1) + j].x;
-          x[j] = make_double2(t.x / d, t.y / d);
-          A[i + (long)(jb + j) * lda] = x[j];       // (stored here: x stays in registers)
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if (tid == 0) a.info[q] = s_fail;
-}
-
-// ---------------------------------------------------------------------------
 // Write the dense factor of q into the tile kernel's planes:
 //   HERK: B[r][c] = conj(L22[c][r]) for c >= r (upper triangular L22^H)
 //   GEMM: B[r][c] = E[r][c]
