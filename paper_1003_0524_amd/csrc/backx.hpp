@@ -1,16 +1,17 @@
 // Back-transform of V^x(k) to the LAPW basis (Sec. III.A, eq. "APW trafo"):
 //   V_GG = Z V Z^H,  Z = S c  (n_G x n_b, S the overlap matrix, c the eigenvectors).
 //
-// Two launches. bt_left_kernel forms T = Z V (n_G x n_b, small: FP64 VALU, one
-// thread per element). bt_gram_kernel forms the n_G x n_G product T Z^H on FP64
-// MFMA in 64 x 64 tiles: wavefront w of a workgroup owns 16 columns of its tile
-// and the tile's 64 rows as four 16 x 16 blocks, each complex block built from
-// four real 16x16x4 products; operands come straight from T and Z (L2-resident,
-// n_b <= 128), 16 values of n per round of loads, and the tile is written once
-// with the 16 lanes of a row group storing 16 consecutive rows of a column (256
-// contiguous bytes). Output bytes
-// dominate for n_b < ~20 (the product has n_b / 2 flop per output byte against
-// the FP64 ridge of ~10), the MFMA work beyond.
+// Two launches on FP64 MFMA in 16 x 16 tiles: bt_left_kernel forms T = Z V (n_G x n_b), bt_gram_kernel, a wavefront
+// per tile, the lower triangle of the n_G x n_G product T Z^H (V is Hermitian, so the product is: the tile above the
+// diagonal is written as the conjugate of the one below). Complex blocks are built from four real 16x16x4 products;
+// operands come straight from Z, V and T (L2-resident, n_b <= 128) into registers, the next 16 values of n requested
+// before the products of these. Rows of C lie along the lanes, so the lower tile is stored in runs of 256 contiguous
+// bytes. Small tiles, so that the stores of some wavefronts overlap the products of others.
+//
+// Output bytes bound it for n_b < ~40 (the half product has n_b / 4 flop per output byte against the FP64 ridge of
+// ~14), the matrix cores beyond. n_G = 2000, n_b = 100 (64 MB out, 1.6 GFLOP, 24 us at the matrix cores' rate): T on
+// the vector cores, an element per thread, 17 -> 8 us; the whole square in 64 x 64 tiles of four wavefronts 68 -> 34 us
+// (the lower triangle in 32 x 32 tiles of one wavefront: 40 us).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>
@@ -19,78 +20,105 @@
 
 namespace exc {
 
-// T[g + n * nG] = sum_m Z[g + m * nG] V[m + n * nb]
-__global__ __launch_bounds__(256) void bt_left_kernel(const double2* __restrict__ Z, const double2* __restrict__ V,
-                                                      int nG, int nb, double2* __restrict__ T) {
-  const int g = blockIdx.x * 256 + threadIdx.x, n = blockIdx.y;
-  if (g >= nG) return;
-  double re = 0.0, im = 0.0;
-#pragma unroll 8
-  for (int m = 0; m < nb; ++m) {                  // (eight loads of Z in flight)
-    const double2 z = Z[g + (long)m * nG], v = V[m + (long)n * nb];
-    re = fma(z.x, v.x, re);
-    re = fma(-z.y, v.y, re);
-    im = fma(z.x, v.y, im);
-    im = fma(z.y, v.x, im);
-  }
-  T[g + (long)n * nG] = make_double2(re, im);
+// re + i im += a b over four values of k, a the lane's value of the A block (row l % 16, k = l / 16), b that of the
+// B block; CONJ: conj(a) b
+template <bool CONJ>
+__device__ __forceinline__ void bt_mac(d4_t& re, d4_t& im, d2_t a, d2_t b) {
+  const double ay = CONJ ? a.y : -a.y;
+  re = mfma(a.x, b.x, re);
+  im = mfma(a.x, b.y, im);
+  re = mfma(ay, b.y, re);
+  im = mfma(-ay, b.x, im);
 }
 
-// C[b + a * nG] = sum_n T[b + n * nG] conj(Z[a + n * nG]) over 64 x 64 tiles: tile t
-// has rows b in (t % nt) * 64 + [0, 64) and columns a in (t / nt) * 64 + [0, 64).
-// As an MFMA product D[a][b] = sum_n conj(Z)[a][n] T[b][n]: the A operand is a
-// 16 x 4 block of conj(Z) (lane l: column a = l % 16, n = l / 16), the B operand a
-// 4 x 16 block of T^T (lane l: row b = l % 16, same n), and lane l holds
-// D[l / 16 + 4 i][l % 16] for i < 4, i.e. C[b0 + l % 16][a0 + l / 16 + 4 i].
-__global__ __launch_bounds__(256) void bt_gram_kernel(const double2* __restrict__ T, const double2* __restrict__ Z,
-                                                      int nG, int nb, double2* __restrict__ C) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int r16 = lane & 15, kq = lane >> 4;
-  const int nt = (nG + 63) / 64;
-  // tiles in turn (grid-stride): the stores of one tile drain while the next one's
-  // operands load and its MFMAs run
-  for (int tile = blockIdx.x; tile < nt * nt; tile += gridDim.x) {
-    const int a0 = (tile / nt) * 64 + 16 * w;       // this wavefront's 16 columns of C
-    const int bt0 = (tile % nt) * 64;                // the tile's 64 rows of C
-    const int a_l = a0 + r16;
-    d4_t accr[4], acci[4];
+// T[g + n * nG] = sum_m Z[g + m * nG] V[m + n * nb] for 16 g (blockIdx.x) and 16 n (blockIdx.y): D[n][g]. Four
+// wavefronts take a quarter of m each (at most 32: every load in flight at once) and add up in LDS.
+__global__ __launch_bounds__(256) void bt_left_kernel(const double2* __restrict__ Z, const double2* __restrict__ V,
+                                                      int nG, int nb, double2* __restrict__ T) {
+  __shared__ double red[3][8][64];
+  const int lane = threadIdx.x & 63, w = uni((int)threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
+  const int g = (int)blockIdx.x * 16 + l16, n = (int)blockIdx.y * 16 + l16;
+  const int kw = ((nb + 15) >> 4) * 4, m0 = w * kw;    // this wavefront's m: [m0, m0 + kw)
+  const double2 *zp = Z + min(g, nG - 1), *vp = V + (long)min(n, nb - 1) * nb;
+  d4_t re{0, 0, 0, 0}, im{0, 0, 0, 0};
+  d2_t z[8], v[8];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) accr[j] = acci[j] = d4_t{0.0, 0.0, 0.0, 0.0};
-    // K in chunks of 16: the chunk's operands (4 of Z, 16 of T per lane) are requested
-    // before its 64 MFMAs, one memory latency per chunk
-    for (int n0 = 0; n0 < nb; n0 += 16) {
-      const int ns = min(4, (nb - n0 + 3) >> 2);     // MFMA steps of 4 in this chunk (uniform)
-      double2 z[4], t[4][4];
+  for (int s = 0; s < 8; ++s) {
+    const int m = m0 + 4 * s + kq;
+    const bool ok = 4 * s < kw && m < nb;
+    const d2_t x = *(const d2_t*)(zp + (long)(ok ? m : 0) * nG), y = *(const d2_t*)(vp + (ok ? m : 0));
+    z[s] = d2_t{ok ? x.x : 0.0, ok ? x.y : 0.0};
+    v[s] = d2_t{ok ? y.x : 0.0, ok ? y.y : 0.0};
+  }
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int n = n0 + 4 * s + kq;
-        z[s] = (a_l < nG && n < nb) ? Z[a_l + (long)n * nG] : make_double2(0.0, 0.0);
+  for (int s = 0; s < 8; ++s) bt_mac<false>(re, im, v[s], z[s]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int b_l = bt0 + 16 * j + r16;
-          t[s][j] = (b_l < nG && n < nb) ? T[b_l + (long)n * nG] : make_double2(0.0, 0.0);
-        }
-      }
-      // conj(z) t = (zr tr + zi ti) + i (zr ti - zi tr)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        if (s >= ns) break;                            // (no MFMAs on the zero tail of n)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          accr[j] = mfma(z[s].x, t[s][j].x, accr[j]);
-          accr[j] = mfma(z[s].y, t[s][j].y, accr[j]);
-          acci[j] = mfma(z[s].x, t[s][j].y, acci[j]);
-          acci[j] = mfma(-z[s].y, t[s][j].x, acci[j]);
-        }
-      }
+  for (int i = 0; i < 4; ++i)
+    if (w > 0) {
+      red[w - 1][i][lane] = re[i];
+      red[w - 1][4 + i][lane] = im[i];
     }
+  __syncthreads();
+  if (w > 0 || g >= nG) return;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int b = bt0 + 16 * j + r16;
+  for (int i = 0; i < 4; ++i) {
+    double x = re[i], y = im[i];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int a = a0 + kq + 4 * i;
-        if (a < nG && b < nG) C[b + (long)a * nG] = make_double2(accr[j][i], acci[j][i]);
+    for (int u = 0; u < 3; ++u) {
+      x += red[u][i][lane];
+      y += red[u][4 + i][lane];
+    }
+    const int c = (int)blockIdx.y * 16 + kq + 4 * i;
+    if (c < nb) T[g + (long)c * nG] = make_double2(x, y);
+  }
+}
+
+// C[b + a * nG] = sum_n T[b + n * nG] conj(Z[a + n * nG]) for the 16 x 16 tiles of rows b >= columns a, and their
+// mirror images: D[a][b] with the A operand conj(Z) and the B operand T, so that lane l holds D[l / 16 + 4 i][l % 16].
+__global__ __launch_bounds__(64, 4) void bt_gram_kernel(const double2* __restrict__ T, const double2* __restrict__ Z,
+                                                        int nG, int nb, double2* __restrict__ C) {
+  const int lane = threadIdx.x, l16 = lane & 15, kq = lane >> 4;
+  const auto rz = make_rsrc(Z, (uint32_t)((long)nG * nb * 16)), rt = make_rsrc(T, (uint32_t)((long)nG * nb * 16));
+  const long nt = (nG + 15) / 16;
+  for (long tile = blockIdx.x; tile < nt * (nt + 1) / 2; tile += gridDim.x) {
+    long tb = (long)((sqrt(8.0 * (double)tile + 1.0) - 1.0) * 0.5);
+    while (tb * (tb + 1) / 2 > tile) --tb;
+    while ((tb + 1) * (tb + 2) / 2 <= tile) ++tb;
+    const int ta = uni((int)(tile - tb * (tb + 1) / 2));
+    const int a0 = ta * 16, b = uni((int)tb) * 16 + l16;
+    // (rows past n_G: the last one again, not stored; n >= nb: past the buffers' ends, zeros)
+    const uint32_t oz = (uint32_t)(min(a0 + l16, nG - 1) + (long)kq * nG) * 16;
+    const uint32_t ot = (uint32_t)(min(b, nG - 1) + (long)kq * nG) * 16;
+    d4_t re{0, 0, 0, 0}, im{0, 0, 0, 0};
+    struct Chunk { d2_t z[4], t[4]; };                 // 16 values of n
+    auto load = [&](Chunk& c, int n0) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const uint32_t o = (uint32_t)(n0 + 4 * s) * (uint32_t)nG * 16;
+        c.z[s] = buf_load<d2_t>(rz, oz + o, 0);
+        c.t[s] = buf_load<d2_t>(rt, ot + o, 0);
+      }
+    };
+    Chunk c0, c1;
+    load(c0, 0);
+    int n0 = 0;
+    for (; n0 + 16 <= nb; n0 += 16) {
+      load(c1, n0 + 16);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) bt_mac<true>(re, im, c0.z[s], c0.t[s]);
+      c0 = c1;
+    }
+    // the last chunk's steps of four (none of them empty)
+    if (n0 < nb) bt_mac<true>(re, im, c0.z[0], c0.t[0]);
+    if (n0 + 4 < nb) bt_mac<true>(re, im, c0.z[1], c0.t[1]);
+    if (n0 + 8 < nb) bt_mac<true>(re, im, c0.z[2], c0.t[2]);
+    if (n0 + 12 < nb) bt_mac<true>(re, im, c0.z[3], c0.t[3]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int a = a0 + kq + 4 * e;
+      if (a < nG && b < nG) {
+        C[b + (long)a * nG] = make_double2(re[e], im[e]);
+        if (ta != (int)tb) C[a + (long)b * nG] = make_double2(re[e], -im[e]);
       }
     }
   }
