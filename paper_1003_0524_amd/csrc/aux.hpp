@@ -606,4 +606,19 @@ __global__ __launch_bounds__(256) void runs_by_row_kernel(const double2* coef, c
   out[e] = v;
 }
 
+// ---------------------------------------------------------------------------
+// Device tables of pointers, written from kernel arguments: in stream order, without a copy from host memory that the
+// host would have to wait for (two such copies and the wait took about 20 us of a call whose kernels take 28).
+// ---------------------------------------------------------------------------
+constexpr int kPtrTab = 64;
+struct PtrTab {
+  void** dst[2];                // second table: nullptr if there is one only
+  int32_t n;
+  void* p[2][kPtrTab];
+};
+__global__ __launch_bounds__(2 * kPtrTab) void put_pointers_kernel(PtrTab t) {
+  const int i = threadIdx.x % kPtrTab, j = threadIdx.x / kPtrTab;
+  if (i < t.n && t.dst[j]) t.dst[j][i] = t.p[j][i];
+}
+
 }  // namespace exc

@@ -195,7 +195,9 @@ struct exc_ctx {
   // pointer tables (device) and their host mirrors
   void** d_mtab = nullptr;
   void** d_vtab = nullptr;
-  std::vector<void*> h_mtab, h_vtab;
+  std::vector<void*> h_mtab, h_vtab;  // what the tables hold, or will once ev_tab has passed
+  hipEvent_t ev_tab = nullptr;
+  bool tab_pending = false;
   int32_t* d_counter = nullptr;
   int persist_grid = 0;
   // graph of the batched path
@@ -339,6 +341,7 @@ void release(exc_ctx* c) {
   c->graph = nullptr;
   release_timing(c);
   if (c->ev_in) hipEventDestroy(c->ev_in);
+  if (c->ev_tab) hipEventDestroy(c->ev_tab);
   if (c->ev_en) hipEventDestroy(c->ev_en);
   c->ev_en = nullptr;
   if (c->ev_out) hipEventDestroy(c->ev_out);
@@ -347,7 +350,7 @@ void release(exc_ctx* c) {
   c->ev_g[0] = c->ev_g[1] = nullptr;
   for (hipEvent_t& e : c->ev_bt) if (e) hipEventDestroy(e);
   c->ev_bt[0] = c->ev_bt[1] = nullptr;
-  c->ev_in = c->ev_out = nullptr;
+  c->ev_in = c->ev_out = c->ev_tab = nullptr;
   c->own = nullptr;
   void* ptrs[] = {c->d_coef, c->d_cvec, c->d_schur, c->d_U, c->d_row_chan, c->d_ch_off,
                   c->d_ch_len, c->d_ch_coef, c->d_rowinfo, c->d_runs, c->d_coefpad, c->d_schunk, c->d_sgroup, c->d_chunk64, c->d_pairs, c->d_pair_w, c->d_pair_begin,
@@ -764,21 +767,63 @@ const KernelCfg* pick_cfg(int mode, int form, int nbt_max) {
   return best;
 }
 
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
+
+// Writes n pointers to one or two device tables, in the order of st.
+exc_status put_pointers(exc_ctx* c, int n, void** dst0, const void* const* src0, void** dst1, const void* const* src1,
+                        hipStream_t st) {
+  for (int i0 = 0; i0 < n; i0 += kPtrTab) {
+    PtrTab t{};
+    t.n = std::min(kPtrTab, n - i0);
+    t.dst[0] = dst0 + i0;
+    t.dst[1] = dst1 ? dst1 + i0 : nullptr;
+    for (int i = 0; i < t.n; ++i) {
+      t.p[0][i] = const_cast<void*>(src0[i0 + i]);
+      t.p[1][i] = dst1 ? const_cast<void*>(src1[i0 + i]) : nullptr;
+    }
+    hipLaunchKernelGGL(put_pointers_kernel, dim3(1), dim3(2 * kPtrTab), 0, st, t);
+  }
+  HIPCHK(c, hipGetLastError());
+  return EXC_OK;
+}
+
 exc_status set_tables(exc_ctx* c, int k0, int nk, const void* const* M, void* const* V,
                       hipStream_t st) {
   bool changed = false;
-  for (int i = 0; i < nk; ++i) {
+  for (int i = 0; i < nk; ++i)
     if (c->h_mtab[k0 + i] != M[i] || c->h_vtab[k0 + i] != V[i]) changed = true;
+  const bool cap = (changed || c->tab_pending) && capturing(st);
+  // the tables may have been written on another stream: after that (a call finds the pointers that it passes
+  // there, whichever call wrote them)
+  if (c->tab_pending && !cap) {
+    if (hipEventQuery(c->ev_tab) == hipSuccess) c->tab_pending = false;
+    else {
+      (void)hipGetLastError();                       // (not ready is not an error)
+      HIPCHK(c, hipStreamWaitEvent(st, c->ev_tab, 0));
+    }
+  } else if (c->tab_pending) {                       // (an event from outside cannot be part of a capture)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    HIPCHK(c, hipThreadExchangeStreamCaptureMode(&mode));
+    const hipError_t e = hipEventSynchronize(c->ev_tab);
+    HIPCHK(c, hipThreadExchangeStreamCaptureMode(&mode));
+    HIPCHK(c, e);
+    c->tab_pending = false;
+  }
+  if (!changed) return EXC_OK;
+  // (a captured call would write the tables at replay only: refused, by the wait below)
+  if (cap) HIPCHK(c, hipStreamSynchronize(st));
+  for (int i = 0; i < nk; ++i) {
     c->h_mtab[k0 + i] = const_cast<void*>(M[i]);
     c->h_vtab[k0 + i] = V[i];
   }
-  if (changed) {
-    HIPCHK(c, hipMemcpyAsync(c->d_mtab + k0, c->h_mtab.data() + k0, nk * sizeof(void*),
-                             hipMemcpyHostToDevice, st));
-    HIPCHK(c, hipMemcpyAsync(c->d_vtab + k0, c->h_vtab.data() + k0, nk * sizeof(void*),
-                             hipMemcpyHostToDevice, st));
-    HIPCHK(c, hipStreamSynchronize(st));   // the host mirrors may change on the next call
-  }
+  TRY(put_pointers(c, nk, c->d_mtab + k0, M, c->d_vtab + k0, (const void* const*)V, st));
+  HIPCHK(c, hipEventRecord(c->ev_tab, st));
+  c->tab_pending = true;
   return EXC_OK;
 }
 
@@ -1884,6 +1929,7 @@ exc_status exchange_init(const exc_desc* d, const exc_coulomb* cv, void* stream,
   }
   IHIP(hipStreamCreateWithFlags(&c->own, hipStreamNonBlocking));
   IHIP(hipEventCreateWithFlags(&c->ev_in, hipEventDisableTiming));
+  IHIP(hipEventCreateWithFlags(&c->ev_tab, hipEventDisableTiming));
   IHIP(hipEventCreateWithFlags(&c->ev_out, hipEventDisableTiming));
   IHIP(hipEventCreateWithFlags(&c->ev_en, hipEventDisableTiming));
   IHIP(hipStreamSynchronize(st));

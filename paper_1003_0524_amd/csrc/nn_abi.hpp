@@ -156,15 +156,16 @@ exc_status learn_scratch(exc_ctx* c) {
   return EXC_OK;
 }
 
-// Copies a host array of n_k device pointers into a device table. The stream
-// is drained first: a previous call's kernels may still read the table.
-exc_status put_table(exc_ctx* c, void* dtab, const void* const* h, hipStream_t st) {
-  if (!h) return fail(c, EXC_EINVAL, "pointer table is NULL");
-  for (int k = 0; k < c->n_k; ++k)
-    if (!h[k]) return fail(c, EXC_EINVAL, "pointer for k=%d is NULL", k);
-  HIPCHK(c, hipStreamSynchronize(st));
-  HIPCHK(c, hipMemcpy(dtab, h, c->n_k * sizeof(void*), hipMemcpyHostToDevice));
-  return EXC_OK;
+// One or two host arrays of n_k device pointers into device tables (h1 null: one), in the order of the stream.
+exc_status put_table(exc_ctx* c, void* dtab, const void* const* h, void* dtab1, const void* const* h1,
+                     hipStream_t st) {
+  for (const void* const* x : {h, dtab1 ? h1 : h}) {
+    if (!x) return fail(c, EXC_EINVAL, "pointer table is NULL");
+    for (int k = 0; k < c->n_k; ++k)
+      if (!x[k]) return fail(c, EXC_EINVAL, "pointer for k=%d is NULL", k);
+  }
+  if (capturing(st)) HIPCHK(c, hipStreamSynchronize(st));   // (not for capture)
+  return put_pointers(c, c->n_k, (void**)dtab, h, (void**)dtab1, h1, st);
 }
 
 }  // namespace
@@ -339,7 +340,7 @@ exc_status exchange_eigh(exc_ctx* c, const void* const* A_k, double* w_out, void
   TRY(learn_scratch(c));
   LearnScratch* l = c->ls;
   hipStream_t st = stream ? (hipStream_t)stream : c->own;
-  TRY(put_table(c, (void*)l->tabA, A_k, st));
+  TRY(put_table(c, (void*)l->tabA, A_k, nullptr, nullptr, st));
   EighArgs a{(const double2* const*)l->tabA, c->d_knb, l->work, (double2*)Z_out, l->z_off, w_out, l->w_off,
              l->sweeps};
   hipLaunchKernelGGL(eigh_jacobi, dim3(c->n_k), dim3(256), 0, st, a);
@@ -361,8 +362,7 @@ exc_status exchange_nn_project(exc_ctx* c, const void* const* Va_k, const void* 
   TRY(learn_scratch(c));
   LearnScratch* l = c->ls;
   hipStream_t st = stream ? (hipStream_t)stream : c->own;
-  TRY(put_table(c, (void*)l->tabA, Va_k, st));
-  TRY(put_table(c, (void*)l->tabB, Vb_k, st));
+  TRY(put_table(c, (void*)l->tabA, Va_k, (void*)l->tabB, Vb_k, st));
   ProjArgs a{(const double2* const*)l->tabA, (const double2* const*)l->tabB, (const double2*)Z, l->z_off,
              c->d_knb, n_blk, scale, y_out, nullptr, nullptr};
   const size_t lds = (size_t)c->nb_max * n_blk * sizeof(double2);
@@ -385,8 +385,7 @@ exc_status exchange_nn_expand(exc_ctx* c, const void* const* Vanchor_k, const vo
   TRY(learn_scratch(c));
   LearnScratch* l = c->ls;
   hipStream_t st = stream ? (hipStream_t)stream : c->own;
-  TRY(put_table(c, (void*)l->tabA, Vanchor_k, st));
-  TRY(put_table(c, (void*)l->tabC, (const void* const*)Vout_k, st));
+  TRY(put_table(c, (void*)l->tabA, Vanchor_k, (void*)l->tabC, (const void* const*)Vout_k, st));
   ProjArgs a{nullptr, nullptr, (const double2*)Z, l->z_off, c->d_knb, n_blk, scale, const_cast<float*>(y),
              (const double2* const*)l->tabA, (double2* const*)l->tabC};
   const size_t lds = (size_t)((n_blk * (n_blk + 1) + 3) / 4) * 16 + (size_t)8 * n_blk * sizeof(double2);
