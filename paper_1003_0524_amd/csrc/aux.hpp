@@ -607,6 +607,77 @@ __global__ __launch_bounds__(256) void runs_by_row_kernel(const double2* coef, c
 }
 
 // ---------------------------------------------------------------------------
+// The partial slot of a pair from the slots of its chunks (fused_kernel with by_chunk): the binary32 Gram sums and the
+// FP64 sums of |Y|^2 over the chunks in the order and rounding of one item that goes through the whole pair.
+// blockIdx.x: Gram tile, or past the last one the sums of |Y|^2; blockIdx.y: pair of the batch. Bound by memory:
+// every chunk is read once, a round of loads ahead of its adds.
+// ---------------------------------------------------------------------------
+struct MergeArgs {
+  const PairInfo* pairs;          // of the batch
+  const int32_t* base;            // [pairs of the batch] first chunk slot
+  const float* chunk;
+  const double* dchunk;           // [slot][wavefront 0..3][column][2]
+  int32_t gstride, ncc;           // ncc: columns of a pass
+  int32_t npass, n_sc;            // n'' passes; chunks of block-sparse rows
+  float* gpart;                   // the pairs' slots
+  double* dpart;
+  int32_t dstride;
+  const uint64_t* tmask;
+};
+__global__ __launch_bounds__(256) void merge_chunks_kernel(MergeArgs a) {
+  __shared__ double D[4 * 128 * 2];
+  const PairInfo& pi = a.pairs[blockIdx.y];
+  const int tp = blockIdx.x, nbt = pi.nb8 >> 3, tid = threadIdx.x;
+  const int ndc = (pi.nd + 63) / 64, cpp = a.n_sc + ndc, n = a.npass * cpp;   // chunks: dense and all of a pass, of the pair
+  const long c0 = a.base[blockIdx.y];
+  if (blockIdx.x + 1 < gridDim.x) {
+    if (tp >= nbt * (nbt + 1) / 2) return;
+    const bool kept = !a.tmask || ((a.tmask[3 * pi.k + (tp >> 6)] >> (tp & 63)) & 1);
+    float x = 0.f;
+    if (kept) {
+      const float* p = a.chunk + c0 * a.gstride + tp * 256 + tid;
+      int c = 0;
+      for (; c + 16 <= n; c += 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = p[(long)(c + u) * a.gstride];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x += v[u];
+      }
+      for (; c < n; ++c) x += p[(long)c * a.gstride];
+    }
+    a.gpart[(long)blockIdx.y * a.gstride + tp * 256 + tid] = x;
+    return;
+  }
+  const int nd2 = 8 * a.ncc;
+  const int per = (a.n_sc ? 1 : 0) + ndc, nt = a.npass * per;         // the slots with sums: of a pass, of the pair
+  auto slot = [&](int i) -> long {                     // the i-th of them
+    const int g = i / per, j = i - g * per;
+    return c0 + (long)g * cpp + (a.n_sc ? (j ? a.n_sc + j - 1 : 0) : j);
+  };
+  for (int e = tid; e < nd2; e += 256) {
+    double x = 0.0;
+    int i = 0;
+    for (; i + 8 <= nt; i += 8) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = a.dchunk[slot(i + u) * nd2 + e];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x += v[u];
+    }
+    for (; i < nt; ++i) x += a.dchunk[slot(i) * nd2 + e];
+    D[e] = x;
+  }
+  __syncthreads();
+  if (tid < pi.nb8) {
+    double s = 0.0;
+    for (int c = tid; c < a.ncc; c += pi.nb8)
+      for (int w = 0; w < 4; ++w) s += D[(w * a.ncc + c) * 2] + D[(w * a.ncc + c) * 2 + 1];
+    a.dpart[(long)blockIdx.y * a.dstride + tid] = s;
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Device tables of pointers, written from kernel arguments: in stream order, without a copy from host memory that the
 // host would have to wait for (two such copies and the wait took about 20 us of a call whose kernels take 28).
 // ---------------------------------------------------------------------------

@@ -15,6 +15,7 @@
 #include <numeric>
 #include <queue>
 #include <string>
+#include <map>
 #include <vector>
 
 #include "../../include/exchange.h"
@@ -113,6 +114,17 @@ struct Plan {
   std::vector<int> order_begin;     //  [launches + 1]: every k at once, or one launch per k or pair
 };
 
+// One k of few pairs in a fused instance that streams its Gram tiles: items per n'' chunk and row part, every chunk of
+// 64 rows in a slot of its own, a batch of pairs at a time.
+struct ChunkPlan {
+  struct Batch { int item0, items, pair0, pairs; };
+  std::vector<Batch> batches;       // (none: one item per pair)
+  WorkItem* d_items = nullptr;
+  int32_t* d_base = nullptr;        // [pairs of k] first chunk slot in the batch
+  int npass = 0;
+  size_t slots = 0;                 // of the largest batch
+};
+
 }  // namespace
 
 struct NnState;        // learned extrapolator (nn_abi.hpp)
@@ -197,6 +209,11 @@ struct exc_ctx {
   void** d_vtab = nullptr;
   std::vector<void*> h_mtab, h_vtab;  // what the tables hold, or will once ev_tab has passed
   hipEvent_t ev_tab = nullptr;
+  std::map<int, ChunkPlan> chunk_plans;    // by k, made at its first call
+  float* d_gchunk = nullptr;
+  double* d_dchunk = nullptr;
+  size_t chunk_cap = 0;               // slots
+  hipEvent_t ev_chunk = nullptr;      // the last use of the chunk slots
   bool tab_pending = false;
   int32_t* d_counter = nullptr;
   int persist_grid = 0;
@@ -325,6 +342,16 @@ void free_plan(Plan& p) {
   p.n_slots = 0;
 }
 
+void free_chunk_plans(exc_ctx* c) {
+  for (auto& kv : c->chunk_plans) { hipFree(kv.second.d_items); hipFree(kv.second.d_base); }
+  c->chunk_plans.clear();
+  hipFree(c->d_gchunk);
+  hipFree(c->d_dchunk);
+  c->d_gchunk = nullptr;
+  c->d_dchunk = nullptr;
+  c->chunk_cap = 0;
+}
+
 void release_timing(exc_ctx* c) {
   for (hipEvent_t e : c->tpool) hipEventDestroy(e);
   c->tpool.clear();
@@ -342,6 +369,8 @@ void release(exc_ctx* c) {
   release_timing(c);
   if (c->ev_in) hipEventDestroy(c->ev_in);
   if (c->ev_tab) hipEventDestroy(c->ev_tab);
+  if (c->ev_chunk) hipEventDestroy(c->ev_chunk);
+  free_chunk_plans(c);
   if (c->ev_en) hipEventDestroy(c->ev_en);
   c->ev_en = nullptr;
   if (c->ev_out) hipEventDestroy(c->ev_out);
@@ -350,7 +379,7 @@ void release(exc_ctx* c) {
   c->ev_g[0] = c->ev_g[1] = nullptr;
   for (hipEvent_t& e : c->ev_bt) if (e) hipEventDestroy(e);
   c->ev_bt[0] = c->ev_bt[1] = nullptr;
-  c->ev_in = c->ev_out = c->ev_tab = nullptr;
+  c->ev_in = c->ev_out = c->ev_tab = c->ev_chunk = nullptr;
   c->own = nullptr;
   void* ptrs[] = {c->d_coef, c->d_cvec, c->d_schur, c->d_U, c->d_row_chan, c->d_ch_off,
                   c->d_ch_len, c->d_ch_coef, c->d_rowinfo, c->d_runs, c->d_coefpad, c->d_schunk, c->d_sgroup, c->d_chunk64, c->d_pairs, c->d_pair_w, c->d_pair_begin,
@@ -1096,13 +1125,136 @@ void launch_k(exc_ctx* c, const Plan& P, int dtype, int k, hipStream_t st) {
   (void)enqueue(L, st);
 }
 
+// One item per pair leaves workgroup slots of the GPU empty when a k has few pairs, and a fused instance that streams
+// its Gram tiles (its binary32 chain runs through the whole pair) cannot be given less than a pair per item without
+// other roundings. Items per n'' chunk and row part that keep every chunk of 64 rows in a slot of its own, added up in
+// the chain's order afterwards, give the same bits from a full GPU: the first V(k) of the ZnO-like workload (144 pairs
+// of 18 n'', bf16x3) 13.4 -> 4.1 ms. The slots are written and read once (12 MB a pair there); batches of pairs keep
+// them within kChunkBytes, about the size of the memory-side cache. A plan without batches: not for this k.
+constexpr size_t kChunkBytes = (size_t)256 << 20;
+exc_status chunk_plan(exc_ctx* c, int k, ChunkPlan** out) {
+  *out = nullptr;
+  const FusedKCfg* f = c->fcfg;
+  if (!c->fused || f->gchain != 1 || f->c64only || c->fsplit != 0) return EXC_OK;
+  const int p0 = c->k_pair[k], p1 = c->k_pair[k + 1];
+  auto found = c->chunk_plans.find(k);
+  if (found == c->chunk_plans.end()) {
+    int n_cu = 256;
+    (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device);
+    ChunkPlan P;
+    std::vector<WorkItem> items;
+    std::vector<int32_t> base;
+    // two workgroups of an instance within half the LDS share a CU
+    const bool few = p1 - p0 < n_cu * (f->lds <= 81920 ? 2 : 1);
+    const int n_sc = c->n_s > 0 ? c->n_schunk : 0;
+    const size_t slot_b = (size_t)c->gstride * 4 + (size_t)64 * f->NCT * 8;
+    size_t slots = 0;                                  // of the batch so far
+    int pb = p0;
+    std::vector<std::pair<double, WorkItem>> bi;       // its items, with their costs
+    auto flush = [&](int pe) {
+      if (pe == pb) return;
+      std::stable_sort(bi.begin(), bi.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
+      P.batches.push_back({(int)items.size(), (int)bi.size(), pb, pe - pb});
+      for (const auto& x : bi) items.push_back(x.second);
+      P.slots = std::max(P.slots, slots);
+      bi.clear();
+      slots = 0;
+      pb = pe;
+    };
+    for (int i = p0; i < p1 && few; ++i) {
+      const PairInfo& p = c->pairs[i];
+      const int nbt = p.nb8 / 8, ngmax = std::max(1, std::min(c->n_occ, f->NCT / nbt));
+      P.npass = (c->n_occ + ngmax - 1) / ngmax;
+      const int ngc = (c->n_occ + P.npass - 1) / P.npass, cpp = n_sc + (p.nd + 63) / 64;
+      const size_t need = (size_t)P.npass * cpp;
+      if (need * slot_b > kChunkBytes) { P = ChunkPlan{}; items.clear(); break; }
+      if ((slots + need) * slot_b > kChunkBytes) flush(i);
+      base.push_back((int32_t)slots);
+      const int nparts = fused_parts(c, p);
+      for (int g = 0; g < P.npass; ++g) {
+        const int g0 = g * ngc, g1 = std::min(c->n_occ, g0 + ngc);
+        for (int part = n_sc ? 0 : 1; part < nparts; ++part) {
+          WorkItem w{};
+          w.pair = i; w.g0 = g0; w.g1 = g1; w.ngc = ngc; w.rb0 = part; w.rb1 = part + 1;
+          w.slot = (int)(slots + (size_t)g * cpp + (part ? n_sc + (part - 1) * f->RTW : 0));
+          bi.push_back({fused_part_cost(c, p, (g1 - g0) * p.nb8, part), w});
+        }
+      }
+      slots += need;
+      if (i + 1 == p1) flush(p1);
+    }
+    if (!P.batches.empty()) {
+      TRY(upload(c, &P.d_items, items));
+      const exc_status s = upload(c, &P.d_base, base);
+      if (s != EXC_OK) { hipFree(P.d_items); return s; }
+    }
+    found = c->chunk_plans.emplace(k, P).first;
+  }
+  ChunkPlan& P = found->second;
+  if (P.batches.empty()) return EXC_OK;
+  if (P.slots > c->chunk_cap) {
+    HIPCHK(c, hipDeviceSynchronize());
+    hipFree(c->d_gchunk);
+    hipFree(c->d_dchunk);
+    c->d_gchunk = nullptr;
+    c->d_dchunk = nullptr;
+    c->chunk_cap = 0;
+    TRY(dalloc(c, &c->d_gchunk, P.slots * c->gstride));
+    TRY(dalloc(c, &c->d_dchunk, P.slots * (size_t)64 * f->NCT));
+    c->chunk_cap = P.slots;
+  }
+  if (!c->ev_chunk) HIPCHK(c, hipEventCreateWithFlags(&c->ev_chunk, hipEventDisableTiming));
+  *out = &P;
+  return EXC_OK;
+}
+
+// The partial slots of k's pairs (those of plan `plan`) through their chunks; the slots of the chunks are shared by
+// every call of the context, whatever its stream.
+exc_status launch_chunks(exc_ctx* c, const ChunkPlan& P, const Plan& plan, int dtype, int k, hipStream_t st) {
+  HIPCHK(c, hipStreamWaitEvent(st, c->ev_chunk, 0));
+  for (const ChunkPlan::Batch& b : P.batches) {
+    MainArgs a;
+    KLaunch L;
+    cfg_tile(c, dtype, k, P.d_items + b.item0, b.items, false, a, L);
+    a.f.gpart = c->d_gchunk;
+    a.f.dpart = c->d_dchunk;
+    a.f.dstride = 64 * c->fcfg->NCT;
+    a.f.by_chunk = 1;
+    (void)enqueue(L, st);
+    const int slot = plan.slot_begin[k] + b.pair0 - c->k_pair[k];
+    MergeArgs m{};
+    m.pairs = c->d_pairs + b.pair0;
+    m.base = P.d_base + (b.pair0 - c->k_pair[k]);
+    m.chunk = c->d_gchunk;
+    m.dchunk = c->d_dchunk;
+    m.gstride = c->gstride; m.dstride = c->dstride; m.ncc = 8 * c->fcfg->NCT;
+    m.npass = P.npass;
+    m.n_sc = c->n_s > 0 ? c->n_schunk : 0;
+    m.gpart = (float*)c->d_gpart + (long)slot * c->gstride;
+    m.dpart = c->d_dpart + (long)slot * c->dstride;
+    m.tmask = c->d_tmask;
+    hipLaunchKernelGGL(merge_chunks_kernel, dim3(c->nbt_max * (c->nbt_max + 1) / 2 + 1, b.pairs), dim3(256), 0, st, m);
+  }
+  HIPCHK(c, hipEventRecord(c->ev_chunk, st));
+  return EXC_OK;
+}
+
 // One k, batched over its q: sparse rows of all pairs of k, one tile launch, reduce.
 exc_status run_k_batched(exc_ctx* c, int k, int dtype, hipStream_t st) {
   if (needs_ws(c)) TRY(ensure_ws(c, c->ws_k_bytes));
   const int p0 = c->k_pair[k], p1 = c->k_pair[k + 1];
   launch_sparse(c, dtype, k, p0, p1 - p0, st);
   const Plan& P = k_plan(c);
-  launch_k(c, P, dtype, k, st);
+  ChunkPlan* cp = nullptr;
+  // (no room for the chunks: one item per pair; a captured call keeps to that too, as its replays may run beside
+  // other calls of the context)
+  if (c->fused && !capturing(st)) {
+    const exc_status s = chunk_plan(c, k, &cp);
+    if (s == EXC_ENOMEM) c->err.clear();
+    else if (s != EXC_OK) return s;
+  }
+  if (cp) TRY(launch_chunks(c, *cp, P, dtype, k, st));
+  else launch_k(c, P, dtype, k, st);
   launch_reduce(c, P, k, 1, st);
   return EXC_OK;
 }
@@ -1311,6 +1463,7 @@ exc_status configure(exc_ctx* c, const FusedKCfg* f, hipStream_t st) {
   free_plan(c->plain);
   free_plan(c->bat);
   free_plan(c->perk);
+  free_chunk_plans(c);
   if (c->h64) {
     if (!c->batched) TRY(build_plan64(c, c->plain, 2, 0));
     else TRY(build_plan64(c, c->bat, 0, c->n_k == 1 ? noalloc_slots(c) : 0));

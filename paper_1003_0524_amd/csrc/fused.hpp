@@ -90,6 +90,10 @@ struct FusedArgs {
   double* dpart;
   int32_t gstride, dstride;
   const uint64_t* tmask;          // [n_k][3] band-tile pairs to compute (bit tp), nullptr: all
+  int32_t by_chunk;               // GSTREAM, items of one row part: every chunk of GR rows to a slot of its own, from
+                                  // the item's on, its FP64 sums of |Y|^2 (Dacc; those of all block-sparse chunks
+                                  // with the first one) to dpart, dstride = NW NCC 2 apart. merge_chunks_kernel adds
+                                  // them up in the order in which one item would.
 };
 
 template <int MODE, int RTW, int NCT, int NB8M, int KC, int CBX = 16, int OCC = 1>
@@ -264,8 +268,9 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
 #pragma unroll
     for (int s = 0; s < NPWR; ++s) gacc[s] = accv_t{0, 0, 0, 0};
     acc_t* gp = (acc_t*)a.gpart + (long)wi.slot * a.gstride;
+    long chunk_slot = wi.slot;
     if constexpr (C::GSTREAM) {
-      for (int s = 0; s < C::NPW; ++s) {
+      for (int s = 0; s < C::NPW && !a.by_chunk; ++s) {
         const int tp = w + NW * s;
         if (tp < npt)
           for (int i = 0; i < 4; ++i) gp[(tp * 4 + i) * 64 + lane] = (acc_t)0;
@@ -309,8 +314,17 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
           if (tp >= npt) break;
           if (!((wkeep >> s) & 1)) continue;
           const accv_t acc = one(tp, accv_t{0, 0, 0, 0});
+          if (a.by_chunk) {                            // (tiles the mask leaves out: not read)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) gp[(tp * 4 + i) * 64 + lane] = acc[i];
+            continue;
+          }
 #pragma unroll
           for (int i = 0; i < 4; ++i) gp[(tp * 4 + i) * 64 + lane] += acc[i];
+        }
+        if (a.by_chunk) {
+          gp += a.gstride;
+          ++chunk_slot;
         }
       } else {
 #pragma unroll
@@ -720,6 +734,13 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
             if (lq == 0) Dacc[(w * NCC + cl) * 2 + part] += d;
           }
           __syncthreads();
+          if constexpr (C::GSTREAM) {
+            if (a.by_chunk)                           // (next added to behind the next barrier)
+              for (int e = tid; e < NW * NCC * 2; e += NT) {
+                a.dpart[chunk_slot * a.dstride + e] = Dacc[e];
+                Dacc[e] = 0.0;
+              }
+          }
           contract_chunk(Ys, ng, std::integral_constant<int, GR>{}, LDR);
         }
       }
@@ -737,7 +758,10 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
       }
     }
     __syncthreads();
-    for (int n = tid; n < nb8; n += NT) {
+    if (C::GSTREAM && a.by_chunk) {
+      if (wi.rb0 == 0)
+        for (int e = tid; e < NW * NCC * 2; e += NT) a.dpart[(long)wi.slot * a.dstride + e] = Dacc[e];
+    } else for (int n = tid; n < nb8; n += NT) {
       double s = 0.0;
       for (int c = n; c < NCC; c += nb8)
         for (int ww = 0; ww < NW; ++ww) s += Dacc[(ww * NCC + c) * 2] + Dacc[(ww * NCC + c) * 2 + 1];
