@@ -634,14 +634,9 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
             if (r0 + 16 * (w + 4 * ii) < min(kc + KC, nd)) n = ii + 1;
           return n;
         };
-        // tiles past the panel's triangle (or past N_d) read zeros through an out-of-range
-        // per-lane offset: the products below run over every tile with no branch, and theirs add
-        // exact zeros
-        auto load_u = [&](int kc, op_t (&u)[RTW][KC / KS][2][NP]) {
-          const int na = n_active(kc);
+        auto load_u = [&](int kc, op_t (&u)[RTW][KC / KS][2][NP], auto tiles) {
 #pragma unroll
-          for (int ii = 0; ii < RTW; ++ii) {
-            const bool act = ii < na;                     // uniform
+          for (int ii = 0; ii < decltype(tiles)::value; ++ii) {
             const long row0 = (long)(r0 + 16 * (w + 4 * ii)) * pi.ldu + kc;
 #pragma unroll
             for (int ks = 0; ks < KC / KS; ++ks)
@@ -649,9 +644,7 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
               for (int h = 0; h < (REALF ? 1 : 2); ++h)
 #pragma unroll
                 for (int p = 0; p < NP; ++p)
-                  u[ii][ks][h][p] = buf_load<op_t>(
-                      urs, act ? u_lane : 0x80000000u,
-                      act ? (uint32_t)(((h * NP + p) * plane + row0 + ks * KS) * C::ESZ) : 0u);
+                  u[ii][ks][h][p] = buf_load<op_t>(urs, u_lane, (uint32_t)(((h * NP + p) * plane + row0 + ks * KS) * C::ESZ));
           }
         };
         const int np = (kend - kc0) / KC;                 // K panels of this row block
@@ -663,17 +656,24 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
           __builtin_amdgcn_s_waitcnt(C::WAIT_VM0);
         }
         lds_barrier();
-        for (int pp = 0; pp < np; ++pp) {
+        // The panels in turn, in RTW + 1 loops: in loop A this wavefront has A active tiles (the count grows with
+        // kc), and only their factor pieces are loaded and their products issued. One loop over all RTW tiles, the
+        // inactive ones on zeros, issues a third too many at N_d = 310: Si-like bf16x3 285 -> 256 us, with inversion
+        // symmetry 137 -> 126 us; a small ragged FP32 system (branches per product before) 127 -> 105 us.
+        int pp = 0;
+        static_for<0, RTW + 1>([&](auto tiles) {
+        constexpr int A = decltype(tiles)::value;
+        for (; pp < np && (A == RTW || n_active(kc0 + pp * KC) == A); ++pp) {
           const int kc = kc0 + pp * KC, buf = C::NRAW == 2 ? (pp & 1) : 0;
-          load_u(kc, ucur);                           // this panel's factor pieces in flight
+          load_u(kc, ucur, tiles);                    // this panel's factor pieces in flight
           convert(kc, buf);
           lds_barrier();                            // pieces ready, raw buffer free
           issue_raw(kc + C::NRAW * KC, buf);
-          const int na = n_active(kc);                // uniform
           // -Im of the h = 1 operand where no -Im plane is staged: a sign-bit mask, no branch
           const uint32_t nmask = part == 0 ? (MODE == M_F32 ? 0x80000000u : 0x80008000u) : 0u;
           // [Yr|Yi] += Br [Ar|Ai] + Bi [-Ai|Ar]: the B operand of step (h, j) is plane
           // part (h = 0) or, for h = 1, -Im (part 0) or Re (part 1); one step ahead
+          if constexpr (A > 0) {
 #pragma unroll
           for (int ks = 0; ks < KC / KS; ++ks) {
             const int kofs = ks * KS + KPL * lq;
@@ -699,17 +699,18 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
 #pragma unroll
               for (int pr = 0; pr < C::T::NPROD; ++pr)
 #pragma unroll
-                for (int ii = 0; ii < RTW; ++ii)
-                  if (MODE != M_F32 || ii < na)   // (fp32: its cheaper products of zero tiles still cost more)
-                    acc[ii][j] = mfma(ucur[ii][ks][h][NP == 1 ? 0 : prod_a(NP, pr)],
-                                      bc[NP == 1 ? 0 : prod_b(NP, pr)], acc[ii][j]);
+                for (int ii = 0; ii < A; ++ii)
+                  acc[ii][j] = mfma(ucur[ii][ks][h][NP == 1 ? 0 : prod_a(NP, pr)],
+                                    bc[NP == 1 ? 0 : prod_b(NP, pr)], acc[ii][j]);
             }
+          }
           }
           // this wave's part of the next panel has landed
           if constexpr (C::NRAW == 2) __builtin_amdgcn_s_waitcnt(C::WAIT_VM_NIW);
           else __builtin_amdgcn_s_waitcnt(C::WAIT_VM0);
           lds_barrier();
         }
+        });
         __builtin_amdgcn_s_waitcnt(C::WAIT_VM0);      // the panels past the end, before the stage takes their place
 
         // ---- the row block's rows through LDS into the Gram tiles, GR rows at a time ----

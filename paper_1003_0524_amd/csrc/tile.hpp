@@ -30,6 +30,8 @@
 // sum of |Y|^2 per band) to its own slot; a separate kernel sums the slots of
 // each k in a fixed order in FP64 (deterministic).
 #pragma once
+#include <utility>
+
 #include "common.hpp"
 
 namespace exc {
@@ -79,6 +81,16 @@ __device__ __forceinline__ uint64_t tile_keep_bits(const uint64_t* tmask, int k,
     if (tp < 192 && ((word >> (tp & 63)) & 1)) r |= 1ull << s;
   }
   return r;
+}
+
+template <int I0, class F, int... I>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I0 + I>{}), ...);
+}
+// f(integral_constant<int, i>) for i = B .. E-1
+template <int B, int E, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (E > B) static_for_impl<B>(f, std::make_integer_sequence<int, E - B>{});
 }
 
 // tile pair index tp <-> (I, J), I <= J, column-wise upper triangle: tp = J(J+1)/2 + I
