@@ -132,6 +132,22 @@ __device__ __forceinline__ void put_realf(typename Traits<MODE>::lds_t* dst, lon
   }
 }
 
+// Four consecutive rows of one column into their NPIECE planes (dst 8-byte aligned; 16 for FP32).
+template <int MODE>
+__device__ __forceinline__ void put_rows4(typename Traits<MODE>::lds_t* dst, long ps, d4_t y) {
+  if constexpr (MODE == M_F32) {
+    *(f4_t*)dst = f4_t{(float)y[0], (float)y[1], (float)y[2], (float)y[3]};
+  } else {
+    constexpr int NP = Traits<MODE>::NPIECE;
+    uint16_t h[4][NP];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) split_d<NP>(y[i], h[i]);
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      *(u2_t*)(dst + p * ps) = u2_t{(uint32_t)h[0][p] | ((uint32_t)h[1][p] << 16), (uint32_t)h[2][p] | ((uint32_t)h[3][p] << 16)};
+  }
+}
+
 // ---------------------------------------------------------------------------
 // MFMA wrappers. A operand: lane l supplies row l%16, k values
 // (KS/4)*(l/16) .. +KS/4-1. B operand: lane l supplies column l%16, same k.

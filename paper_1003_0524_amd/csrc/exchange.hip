@@ -162,6 +162,11 @@ struct exc_ctx {
   double2* d_coefpad = nullptr;       // fused kernel: padded coefficient runs (see FusedArgs)
   int4* d_schunk = nullptr;           // fused kernel: chunks of whole channels (see FusedArgs)
   uint2* d_sgroup = nullptr;          // fused kernel: row groups of each chunk (see FusedArgs)
+  RowUnits row_units{};               // fused kernels: the block-sparse rows in operand order (rows.hpp)
+  RowUnit* d_units = nullptr;
+  int32_t* d_ucount = nullptr;
+  int2* d_uowner = nullptr;
+  d2_t* d_uw = nullptr;
   std::vector<int4> h_schunk;
   int n_schunk = 0;
   int64_t* d_ch_coef = nullptr;
@@ -382,7 +387,7 @@ void release(exc_ctx* c) {
   c->ev_in = c->ev_out = c->ev_tab = c->ev_chunk = nullptr;
   c->own = nullptr;
   void* ptrs[] = {c->d_coef, c->d_cvec, c->d_schur, c->d_U, c->d_row_chan, c->d_ch_off,
-                  c->d_ch_len, c->d_ch_coef, c->d_rowinfo, c->d_runs, c->d_coefpad, c->d_schunk, c->d_sgroup, c->d_chunk64, c->d_pairs, c->d_pair_w, c->d_pair_begin,
+                  c->d_ch_len, c->d_ch_coef, c->d_rowinfo, c->d_runs, c->d_coefpad, c->d_schunk, c->d_sgroup, c->d_units, c->d_ucount, c->d_uowner, c->d_uw, c->d_chunk64, c->d_pairs, c->d_pair_w, c->d_pair_begin,
                   c->d_ws, c->d_dsp, c->d_gpart, c->d_dpart, c->d_vres, c->d_voff, c->d_knb,
                   c->d_mtab, c->d_vtab, c->d_counter, c->d_mstage, c->d_eout, c->d_ewk, c->d_erho,
                   c->d_gamma, c->d_gpartial, c->d_bt, c->d_tmask, c->d_ppairs, c->d_pw, c->d_pg,
@@ -902,6 +907,7 @@ FusedArgs fused_args(exc_ctx* c, int dtype) {
   f.row_chan = c->d_row_chan; f.ch_off = c->d_ch_off; f.ch_len = c->d_ch_len; f.ch_coef = c->d_ch_coef;
   f.coef = c->d_coef; f.cvec = c->d_cvec; f.rowinfo = c->d_rowinfo; f.coefpad = c->d_coefpad;
   f.schunk = c->d_schunk; f.n_schunk = c->n_schunk; f.sgroup = c->d_sgroup;
+  f.rows = c->row_units;
   f.coef_qs = c->nqc > 1 ? c->coef_total : 0;
   f.cvec_qs = c->nqc > 1 ? c->n_s : 0;
   f.pad_qs = c->nqc > 1 ? (int64_t)std::max(1, c->n_schunk) * kChunkRows * kRunPad : 0;
@@ -1820,6 +1826,47 @@ exc_status exchange_init(const exc_desc* d, const exc_coulomb* cv, void* stream,
       }
       std::vector<int4> ck = c->h_schunk;
       c->n_schunk = (int)ck.size();
+      if (c->n_schunk) {
+        // each chunk's groups of 16 rows: units of eight rows of M from the group's first row to the end of its last
+        // channel, then of its channels' multipole rows
+        std::vector<RowUnit> units;
+        std::vector<int2> owner;
+        std::vector<int32_t> count;
+        RowUnits& R = c->row_units;
+        for (int t = 0; t < 4; ++t) {
+          R.begin[t] = (int)units.size();
+          for (const int4& x : ck) {
+            const size_t at = units.size();
+            const int r0 = x.x + 16 * t, n = std::min(16, x.y - 16 * t);
+            auto add = [&](int row, int end) {
+              for (; row < end; row += 8) {
+                units.push_back({row, std::min(8, end - row)});
+                owner.push_back(make_int2(r0, n));
+              }
+            };
+            if (n > 0) {
+              const int ch0 = row_chan[r0], ch1 = row_chan[r0 + n - 1];
+              add(r0, (int)c->ch_off[ch1] + (int)c->ch_len[ch1]);
+              add(c->n_s + ch0, c->n_s + ch1 + 1);
+              while ((units.size() - at) % kUnitRing) {
+                units.push_back({0, 0});
+                owner.push_back(make_int2(r0, n));
+              }
+            }
+            count.push_back((int)(units.size() - at));
+          }
+        }
+        ITRY(upload(c, &c->d_units, units));
+        ITRY(upload(c, &c->d_uowner, owner));
+        ITRY(upload(c, &c->d_ucount, count));
+        ITRY(dalloc(c, &c->d_uw, units.size() * 128 * c->nqc));
+        R.units = c->d_units;
+        R.count = c->d_ucount;
+        R.n_chunk = c->n_schunk;
+        R.n_units = (int)units.size();
+        R.w = c->d_uw;
+        R.w_qs = c->nqc > 1 ? (int64_t)units.size() * 128 : 0;
+      }
       if (ck.empty()) ck.push_back(make_int4(0, 0, 0, 0));
       ITRY(upload(c, &c->d_schunk, ck));
       // row groups of each chunk: its kChunkRows rows (those past the chunk with run length 0)
@@ -1931,6 +1978,11 @@ exc_status exchange_init(const exc_desc* d, const exc_coulomb* cv, void* stream,
       hipLaunchKernelGGL(pad_runs_kernel, dim3((unsigned)((ne + 255) / 256), c->nqc), dim3(256), 0, st, c->d_coef,
                          c->d_rowinfo, c->d_schunk, c->n_schunk, kRunPad, kChunkRows, c->d_coefpad,
                          c->nqc > 1 ? c->coef_total : (int64_t)0);
+      // the fused kernels' operands of the block-sparse rows, from the (now factored) channel coefficients
+      if (c->n_schunk)
+        hipLaunchKernelGGL(pack_units_kernel, dim3(c->row_units.n_units, c->nqc), dim3(128), 0, st, c->row_units,
+                           c->d_uowner, c->d_coef, c->d_cvec, c->d_rowinfo, c->n_s,
+                           c->nqc > 1 ? c->coef_total : (int64_t)0, c->nqc > 1 ? (int64_t)c->n_s : (int64_t)0, c->d_uw);
       if (c->d_runs) {
         // sparse_kernel's runs of the factored channel coefficients, row by row
         const long nr = (long)c->run_max * c->runs_ld;

@@ -28,9 +28,10 @@
 //
 // Bound by the issue of operand reads and products; the panels' loads stay in flight across the barriers of the K
 // loop (see lds_barrier): one outer iteration of the Si-like workload in bf16x3 289 -> 285 us, with its inversion
-// symmetry 140 -> 137 us.
+// symmetry 140 -> 137 us (further down: to 254 and 126).
 #pragma once
 #include "common.hpp"
+#include "rows.hpp"
 #include "tile.hpp"
 
 #include <type_traits>
@@ -83,6 +84,8 @@ struct FusedArgs {
   const int4* rowinfo;            // per multipole-free row r of channel c (r = first row + i):
                                   // {index in coef of conj-coefficient run L_c[i..b-1][i], b - i,
                                   //  multipole row n_s + c, 0}
+  RowUnits rows;                  // the same rows in operand order, for the instances that form them on the
+                                  // matrix cores (rows.hpp)
   const uint2* sgroup;            // per chunk, 16 groups of four of its 64 rows (rows past the chunk
                                   // with run length 0) by decreasing run length: {rows (one byte
                                   // each), longest run}
@@ -125,6 +128,10 @@ struct FusedCfg {
   // binary32 Gram chains (for error models): one per item, or (GSTREAM) one per GR-row
   // chunk added into the item's partial; GR rows per chunk in both row kinds
   static constexpr int GCHAIN = GSTREAM ? 1 : 0, GCH_RS = GR, GCH_RD = GR;
+  // the block-sparse rows on the FP64 matrix cores (rows.hpp): a small ragged FP32 system (8 column tiles) 105 -> 90 us.
+  // Elsewhere the vector cores stay ahead: Si-like bf16x3 256 us against 272, FP32 (6 column tiles) 477 against 506.
+  // (Real-factor instances would gain, 126 -> 114 us, but give the bits of their general twins.)
+  static constexpr bool MFMA_ROWS = MODE == M_F32 && NCT > 6;
   static constexpr int CB = CBX;                         // sparse step: columns (CB / NW per wavefront)
   static constexpr int CPW = CB / NW;
   static constexpr int NCB = (NCC + CB - 1) / CB;        // column blocks of a sparse chunk (at most)
@@ -359,7 +366,43 @@ __global__ __launch_bounds__(256, OCC) void fused_kernel(FusedArgs a) {
       // The workgroup meets once per chunk, when every column is staged, to contract it.
       // The FP64 sums of |Y|^2 stay in registers, one per lane (row) and column, and are
       // summed over the rows once at the end.
-      if (a.n_s > 0 && wi.rb0 == 0) {
+      // The larger FP32 instances: on the matrix cores instead (rows.hpp), wavefront w rows 16 w .. + 15 of every chunk.
+      if constexpr (C::MFMA_ROWS) {
+        if (a.rows.n_chunk > 0 && wi.rb0 == 0) {
+          int lx = lane;                                // (see tid_o)
+          asm volatile("" : "+v"(lx));
+          const int sc = (lx & 15) >> 1, sp = lx & 1, sq = lx >> 4;   // column of a tile, Re / Im, rows 4 sq ..
+          lds_t* Sl = Ys + (sp * NP) * YPL + sc * LDR + 16 * w + 4 * sq;
+          uint32_t co[NCT];
+          double dreg[NCT];
+#pragma unroll
+          for (int j = 0; j < NCT; ++j) {
+            int n = 0;
+            const long col = col_index(8 * j + sc, n);
+            co[j] = 8 * j + sc < ncols && n < nb ? (uint32_t)(col * pi.nmb * esz) : 0x80000000u;
+            dreg[j] = 0.0;
+          }
+          __syncthreads();                              // earlier users of the LDS are done
+          sparse_units<NCT, REALF, false, 2>(a.rows, pi.q, mrs, co, ncols >> 3, a.m_c64, w, lx, [&](int, const d4_t (&y)[NCT]) {
+#pragma unroll
+            for (int j = 0; j < NCT; ++j) {
+              put_rows4<MODE>(Sl + j * 8 * LDR, YPL, y[j]);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) dreg[j] = fma(y[j][e], y[j][e], dreg[j]);
+            }
+            lds_barrier();
+            contract_chunk(Ys, ng, std::integral_constant<int, GR>{}, LDR);
+            lds_barrier();                              // the stage is free
+          });
+#pragma unroll
+          for (int j = 0; j < NCT; ++j) {
+            double d = dreg[j];
+            d += __shfl_xor(d, 16);
+            d += __shfl_xor(d, 32);
+            if (sq == 0) Dacc[(w * NCC + 8 * j + sc) * 2 + sp] += d;
+          }
+        }
+      } else if (a.n_s > 0 && wi.rb0 == 0) {
         constexpr int CB = C::CB, CPW = C::CPW, NCB = C::NCB, MAXT = C::MAXT, CFL = C::CFL, MPC = C::MPC;
         const int nck = a.n_schunk;
         const int ncb = (ncols + CB - 1) / CB;

@@ -22,7 +22,8 @@
 //
 // Bound by the matrix cores and the operand reads between barriers. Requests that really stay in flight across the
 // barriers (see lds_barrier) took the ZnO-like workload, 2 k, from 4.37 to 4.12 ms in bf16x3 and, 2 k of 72 q, from
-// 3.08 to 2.99 ms in bf16x6; the SrTiO3-like one, 2 k of 108 q, from 13.55 to 12.95 ms in bf16x3.
+// 3.08 to 2.99 ms in bf16x6; the SrTiO3-like one, 2 k of 108 q, from 13.55 to 12.95 ms in bf16x3 (further down: to
+// 4.02, 2.85 and 11.54 ms).
 #pragma once
 #include "fused.hpp"
 
@@ -114,6 +115,10 @@ struct WideCfg {
   // factor loads per wavefront and panel: each lane takes 8 consecutive k of a row per piece
   // plane (one 16-byte load for bf16 pieces, two for FP32)
   static constexpr int NFL = RT * 2 * (MODE == M_F32 ? 2 : NP);
+  // the block-sparse rows on the FP64 matrix cores (rows.hpp): SrTiO3-like (13 band tiles) bf16x3 12.95 -> 11.71 ms,
+  // one k of 48 q in FP32 7.05 -> 6.90, in bf16x6 4.84 -> 4.63; up to 8 band tiles the vector cores stay ahead
+  // (ZnO-like 4.02 ms against 4.18)
+  static constexpr bool MFMA_ROWS = NCT > 8;
   // block-sparse phase: a chunk of at most GR rows (whole channels) and its at most MPC
   // multipole rows; the chunk's M values are staged in LDS, XC columns at a time (all of the
   // item's columns where they fit beside the Gram stage), rows [GR + MPC] x columns, with an
@@ -471,7 +476,50 @@ __global__ __launch_bounds__(512, 1) void wide_kernel(FusedArgs a) {
       // LDS read per term and column). The FP64 sums of |Y|^2 stay in registers, one per lane and column group. The
       // next stage's values come to registers while the current one runs; the workgroup meets
       // twice per stage (stage written, stage read) and once per chunk to contract its rows.
-      if (a.n_s > 0 && wi.rb0 == 0) {
+      // More than 8 band tiles: on the matrix cores instead (rows.hpp), wavefront w rows 16 (w % 4) .. + 15 of every
+      // chunk and half of the column tiles.
+      if constexpr (C::MFMA_ROWS) {
+        if (a.rows.n_chunk > 0 && wi.rb0 == 0) {
+          constexpr int NJ = (NCT + 1) / 2, LDRS = C::LDRS;
+          int lx = lane;
+          asm volatile("" : "+v"(lx));
+          const int sc = (lx & 15) >> 1, sp = lx & 1, sq = lx >> 4;   // column of a tile, Re / Im, rows 4 sq ..
+          const int j0 = (w >> 2) * NJ, nj = min(NJ, NCT - j0);       // this wavefront's column tiles
+          lds_t* Sl = (lds_t*)smem + (sp * NP) * NCC * LDRS + (8 * j0 + sc) * LDRS + 16 * (w & 3) + 4 * sq;
+          uint32_t co[NJ];
+          double dreg[NJ];
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            const int c = 8 * (j0 + j) + sc;
+            int n = 0;
+            const long col = col_index(c, n);
+            co[j] = j < nj && c < ncols && n < nb ? (uint32_t)(col * pi.nmb * esz) : 0x80000000u;
+            dreg[j] = 0.0;
+          }
+          __syncthreads();                                      // earlier users of the LDS are done
+          sparse_units<NJ, false, true, 2>(a.rows, pi.q, mrs, co, min(nj, (ncols >> 3) - j0), true, w & 3, lx,
+                                  [&](int, const d4_t (&y)[NJ]) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+              if (j < nj) {
+                put_rows4<MODE>(Sl + j * 8 * LDRS, NCC * LDRS, y[j]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dreg[j] = fma(y[j][e], y[j][e], dreg[j]);
+              }
+            lds_barrier();
+            contract((const lds_t*)smem, ng, std::integral_constant<int, GR>{}, LDRS, std::true_type{});
+            lds_barrier();                                      // the stage is free
+          });
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            if (j < nj) {
+              double d = dreg[j];
+              d += __shfl_xor(d, 16);
+              d += __shfl_xor(d, 32);
+              if (sq == 0) Dacc[(w * NCC + 8 * (j0 + j) + sc) * 2 + sp] += d;
+            }
+        }
+      } else if (a.n_s > 0 && wi.rb0 == 0) {
         constexpr int MAXT = C::MAXT, MPC = C::MPC, XC = C::XC, XP = C::XP, NU = C::NU;
         constexpr int NDR = C::NDR, XLD = C::XLD, XLM = C::XLM, LDRS = C::LDRS;
         const int nck = a.n_schunk;
@@ -812,13 +860,12 @@ __global__ __launch_bounds__(512, 1) void wide_kernel(FusedArgs a) {
         wait_vm<(NRAW - 2) * NIW + NFL>();                // own part of raw panel 1 landed
         lds_barrier();
 
-        // The panels in turn, for up to 8 band tiles in RT + 1 loops: in loop A this wavefront has A active row tiles
-        // (the count grows with kc), and only their products are issued (ZnO-like, bf16x3 4.12 -> 4.03 ms, bf16x6
-        // 2.99 -> 2.85 ms). With more band tiles, whose accumulators leave few registers, one loop: all tiles where
-        // one is active, the others on zeros (SrTiO3-like 12.95 ms, in RT + 1 loops 13.11).
-        constexpr bool BY_TILES = NCT <= 8;
+        // The panels in turn, in RT + 1 loops: in loop A this wavefront has A active row tiles (the count grows with
+        // kc), and only their products are issued. One loop, all tiles where one is active and the others on zeros:
+        // ZnO-like bf16x3 4.12 ms where this takes 4.02, bf16x6 2.99 and 2.85; SrTiO3-like (13 band tiles) bf16x3
+        // 11.71 and 11.54, one k of 48 q in FP32 6.90 and 6.65, in bf16x6 4.63 and 4.46.
         int p = 0;
-        static_for<BY_TILES ? 0 : RT, RT + 1>([&](auto tiles_c) {
+        static_for<0, RT + 1>([&](auto tiles_c) {
         constexpr int A = decltype(tiles_c)::value;
         for (; p < np && (A == RT || n_active(kc0 + p * KC) == A); ++p) {
           const int kc = kc0 + p * KC;
@@ -890,7 +937,7 @@ __global__ __launch_bounds__(512, 1) void wide_kernel(FusedArgs a) {
               }
             }
           };
-          const bool act = BY_TILES ? A > 0 : n_active(kc) > 0;
+          constexpr bool act = A > 0;
           if (act) panel(std::integral_constant<int, 0>{});
           else if (conv) convert_half(kc + KC, (p + 1) % NRAW, (p + 1) & 1, 0);
           mid();
