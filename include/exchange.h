@@ -375,6 +375,12 @@ exc_status exchange_timing(exc_ctx *ctx, int32_t n_slots);
  * outputs. Training: full-batch Adam (beta1 0.9, beta2 0.999, eps 1e-8, bias
  * correction), one step per epoch. Samples are rows: X is n x in, Y is n x out.
  * The network belongs to the context (one per context) and lives on its GPU.
+ *
+ * Streams: with a stream a call on device arrays is ordered on it and asynchronous
+ * (exchange_nn_train and _grad take none and are synchronous). NULL = the default
+ * stream: the call is ordered after everything queued on it and returns when its
+ * results are there. Each learned call of a context is ordered after the one before it,
+ * whatever their streams.
  * ========================================================================== */
 
 /* exchange_nn_init -- create (or replace) the context's network. Weights are
@@ -402,8 +408,7 @@ exc_status exchange_nn_grad(exc_ctx *ctx, const float *X, const float *Y, int32_
                             float *grad_out, float *loss_out);
 
 /* exchange_nn_predict -- Y_out (n x out) = network(X). Host pointers: the
- * call returns when Y_out is written. Device pointers with a stream: ordered
- * on that stream, asynchronous. */
+ * call returns when Y_out is written. Device pointers: as under "Streams" above. */
 exc_status exchange_nn_predict(exc_ctx *ctx, const float *X, int32_t n, float *Y_out, int32_t on_device,
                                void *stream);
 
@@ -413,8 +418,7 @@ exc_status exchange_nn_predict(exc_ctx *ctx, const float *X, int32_t n, float *Y
  * With v = P_new - P_old: x_out[i] = sum_j S_ij v_j / |v| (device, m floats,
  * zero if v = 0), S_ij = -1/sqrt(m) if the top bit of SplitMix64(seed) output
  * number i*n_real + j is set, else +1/sqrt(m); *norm_out (device double) =
- * |v|. 1 <= m <= 128. Asynchronous on stream (NULL: the context's stream,
- * synchronous). */
+ * |v|. 1 <= m <= 128. */
 exc_status exchange_nn_features(exc_ctx *ctx, const double *P_new, const double *P_old, int64_t n_real,
                                 uint64_t seed, int32_t m, float *x_out, double *norm_out, void *stream);
 

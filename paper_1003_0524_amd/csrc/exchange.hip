@@ -228,6 +228,7 @@ struct exc_ctx {
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   hipEvent_t ev_en = nullptr;         // end of the last energy call (its buffers are shared)
   bool ev_en_set = false;
+  hipEvent_t ev_learn = nullptr;      // end of the last learned call (its buffers are shared)
   int g_dtype = -1;
   // live kernel timing of the batched path: event-record nodes around the
   // sparse and tile kernels; one pool entry (3 events) per graph replay
@@ -377,7 +378,8 @@ void release(exc_ctx* c) {
   if (c->ev_chunk) hipEventDestroy(c->ev_chunk);
   free_chunk_plans(c);
   if (c->ev_en) hipEventDestroy(c->ev_en);
-  c->ev_en = nullptr;
+  if (c->ev_learn) hipEventDestroy(c->ev_learn);
+  c->ev_en = c->ev_learn = nullptr;
   if (c->ev_out) hipEventDestroy(c->ev_out);
   if (c->own) hipStreamDestroy(c->own);
   for (hipEvent_t& e : c->ev_g) if (e) hipEventDestroy(e);
