@@ -1900,11 +1900,11 @@ exc_status exchange_init(const exc_desc* d, const exc_coulomb* cv, void* stream,
     std::vector<int32_t> e_ld(c->n_q), nd32(c->nd.begin(), c->nd.end()), ldu32(c->ldu.begin(), c->ldu.end());
     int64_t e_total = 0;
     for (int q = 0; q < c->n_q; ++q) { e_off[q] = e_total; e_ld[q] = std::max(1, c->nd[q]); e_total += (int64_t)c->nd[q] * c->nd[q]; }
-    double2 *d_E = nullptr, *d_inv = nullptr;
+    double2* d_E = nullptr;
     int64_t *d_eoff = nullptr, *d_uoff = nullptr;
     int32_t *d_nd = nullptr, *d_eld = nullptr, *d_ldu = nullptr;
     int* d_info = nullptr;
-    auto cleanup = [&]() { hipFree(d_E); hipFree(d_inv); hipFree(d_eoff); hipFree(d_uoff); hipFree(d_nd); hipFree(d_eld); hipFree(d_ldu); hipFree(d_info); };
+    auto cleanup = [&]() { hipFree(d_E); hipFree(d_eoff); hipFree(d_uoff); hipFree(d_nd); hipFree(d_eld); hipFree(d_ldu); hipFree(d_info); };
     exc_status s = dalloc(c, &d_E, (size_t)e_total);
     if (s != EXC_OK) { cleanup(); return bail(s); }
     for (int q = 0; q < c->n_q; ++q) {
@@ -1924,8 +1924,7 @@ exc_status exchange_init(const exc_desc* d, const exc_coulomb* cv, void* stream,
     }
     if ((s = upload(c, &d_eoff, e_off)) != EXC_OK || (s = upload(c, &d_uoff, c->u_off)) != EXC_OK ||
         (s = upload(c, &d_nd, nd32)) != EXC_OK || (s = upload(c, &d_eld, e_ld)) != EXC_OK ||
-        (s = upload(c, &d_ldu, ldu32)) != EXC_OK || (s = dalloc(c, &d_info, (size_t)c->n_q + 1)) != EXC_OK ||
-        (s = dalloc(c, &d_inv, (size_t)c->n_q * 1024)) != EXC_OK) {
+        (s = upload(c, &d_ldu, ldu32)) != EXC_OK || (s = dalloc(c, &d_info, (size_t)c->n_q + 1)) != EXC_OK) {
       cleanup(); return bail(s);
     }
     hipMemsetAsync(d_info, 0, (c->n_q + 1) * sizeof(int), st);
@@ -1939,7 +1938,7 @@ exc_status exchange_init(const exc_desc* d, const exc_coulomb* cv, void* stream,
                            c->d_schur, d_info + c->n_q, c->nqc > 1 ? c->coef_total : (int64_t)0,
                            c->nqc > 1 ? (int64_t)c->n_s : (int64_t)0);
       CholArgs ca{d_E, d_eoff, d_nd, d_eld, c->n_ch, c->n_ch ? c->d_schur : nullptr,
-                  c->nqc > 1 ? c->n_ch : 0, d_info, d_inv, 0};
+                  c->nqc > 1 ? c->n_ch : 0, d_info, 0};
       const int nblk = (*std::max_element(c->nd.begin(), c->nd.end()) + kCholBlock - 1) / kCholBlock;
       for (; ca.jb < nblk; ++ca.jb) {
         hipLaunchKernelGGL(chol_update_kernel, dim3(c->n_q, nblk - ca.jb), dim3(256), 0, st, ca);
