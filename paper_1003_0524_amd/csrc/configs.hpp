@@ -3,6 +3,7 @@
 #pragma once
 #include "fused.hpp"
 #include "herk64.hpp"
+#include "plan64.hpp"
 
 namespace exc {
 
@@ -35,10 +36,10 @@ extern const FusedKCfg kWideCfgs[kNumWide];
 // FP64 Cholesky/HERK kernels (herk64.hpp): nbt band tiles, ng n'' values per pass. The planner picks
 // the smallest nbt that holds the context's bands and the ng of the cheapest plan (build_plan64).
 struct Herk64K {
-  int nbt, ng, nw, npw, ctw;
+  Shape64 shape;
   void (*fn)(Herk64Args);           // complex128 M
   void (*fn64)(Herk64Args);         // complex64 M
-  int id() const { return 2000 + 16 * nbt + ng; }
+  int id() const { return 2000 + 16 * shape.nbt + shape.ng; }
 };
 extern const Herk64K kHerk64[kNumHerk64];
 

@@ -4,8 +4,8 @@
 namespace exc {
 
 #define HCFG(NBT, NG)                                                                              \
-  Herk64K{NBT, NG, Herk64Cfg<NBT, NG, false>::NW, Herk64Cfg<NBT, NG, false>::NPW,                   \
-          Herk64Cfg<NBT, NG, false>::CTW, herk64_kernel<NBT, NG, false>, herk64_kernel<NBT, NG, true>}
+  Herk64K{{NBT, NG, Herk64Cfg<NBT, NG, false>::NW, Herk64Cfg<NBT, NG, false>::NPW,                  \
+           Herk64Cfg<NBT, NG, false>::CTW}, herk64_kernel<NBT, NG, false>, herk64_kernel<NBT, NG, true>}
 const Herk64K kHerk64[kNumHerk64] = {
     HCFG(1, 1), HCFG(1, 2), HCFG(1, 4), HCFG(1, 8), HCFG(1, 12),
     HCFG(2, 1), HCFG(2, 2), HCFG(2, 3), HCFG(2, 4), HCFG(2, 6),

@@ -13,7 +13,6 @@
 #include <cstring>
 #include <mutex>
 #include <numeric>
-#include <queue>
 #include <string>
 #include <map>
 #include <vector>
@@ -578,66 +577,19 @@ exc_status build_plan(exc_ctx* c, Plan& P, int split_rows) {
   return EXC_OK;
 }
 
-// ---------------------------------------------------------------------------
-// Work items of the FP64 Cholesky/HERK kernel. An item is a pair, a run of n'' values and a run of
-// row parts (part 0 the block-sparse rows, part 1 + j the dense rows [64 j, 64 j + 64)); costs are in
-// matrix instructions of one wavefront (64 cycles each).
-// ---------------------------------------------------------------------------
-struct Split64 {
-  const Herk64K* k = nullptr;
-  int passes = 1;                   // n'' passes per item (0: all)
-  int groups = 1;                   // runs of row parts per pair (0: one item per part)
-};
-
-double part_cost64(const exc_ctx* c, const Herk64K& k, const PairInfo& p, int part) {
-  const bool regg = k.nbt <= 3;
-  const int npt = k.nbt * (k.nbt + 1) / 2;
-  const int gram = regg ? 4 * k.ng * npt : 16 * k.npw * k.ng + 12;      // of 64 rows
-  // block-sparse rows: four chunks at a time formed by five steps, or 16 rows at a time read from the workspace
-  if (part == 0)
-    return c->n_chunk64 ? (double)((c->n_chunk64 + 3) / 4) * (10 * k.ctw + gram)
-                        : (double)((c->n_s + 15) / 16) * std::max(10, gram / 4);
-  const int np = (p.nd - 64 * (part - 1) + 15) / 16;
-  // (a panel shorter than its barrier and loads costs those)
-  return (double)np * std::max(12, 8 * k.ctw + 2) + gram + 10;
-}
-
-// The items of one pair under a split, through push(g0, g1, part0, part1, cost).
-template <class F>
-void split_pair64(const exc_ctx* c, const Split64& sp, const PairInfo& p, F&& push) {
-  const Herk64K& k = *sp.k;
-  const int nparts = 1 + (p.nd + 63) / 64, first = c->n_s > 0 ? 0 : 1;
-  const int npass = (c->n_occ + k.ng - 1) / k.ng, per = sp.passes ? sp.passes : npass;
-  std::vector<double> pc(nparts, 0.0);
-  double tot = 0.0;
-  for (int i = first; i < nparts; ++i) tot += pc[i] = part_cost64(c, k, p, i);
-  for (int g = 0; g < npass; g += per) {
-    const int n = std::min(per, npass - g), g0 = g * k.ng, g1 = std::min(c->n_occ, (g + n) * k.ng);
-    int at = first;
-    double left = tot;
-    for (int r = sp.groups ? sp.groups : nparts; at < nparts; --r) {
-      // the next run: parts until its share of what is left is reached
-      const double want = r > 1 ? left / r : 1e300;
-      double cs = pc[at];
-      int e = at + 1;
-      while (e < nparts && sp.groups && cs + 0.5 * pc[e] <= want) cs += pc[e++];
-      push(g0, g1, at, e, cs * n);
-      left -= cs;
-      at = e;
-    }
-  }
-}
-
 // Launch order: the hardware deals workgroup b to XCD b mod 8. Items of one q share its factor, so q are
 // dealt to eight lists by decreasing cost, each list in order of decreasing cost, the lists interleaved (and
 // padded); where few q leave the lists uneven, one list over all items instead.
 void order64(const exc_ctx* c, const std::vector<WorkItem>& it, const std::vector<double>& cost, int i0, int i1,
              std::vector<WorkItem>& out) {
-  std::vector<int> ord(i1 - i0);
-  std::iota(ord.begin(), ord.end(), i0);
-  std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return cost[a] > cost[b]; });
+  struct Item { double cost; int i, q; };
+  std::vector<Item> ord;
+  ord.reserve(i1 - i0);
+  for (int i = i0; i < i1; ++i) ord.push_back({cost[i], i, c->pairs[it[i].pair].q});
+  auto more = [](const Item& a, const Item& b) { return a.cost > b.cost; };
+  if (!std::is_sorted(ord.begin(), ord.end(), more)) std::stable_sort(ord.begin(), ord.end(), more);
   std::vector<double> qc(c->n_q, 0.0), load(8, 0.0);
-  for (int i : ord) qc[c->pairs[it[i].pair].q] += cost[i];
+  for (const Item& x : ord) qc[x.q] += x.cost;
   std::vector<int> qo(c->n_q), qof(c->n_q, 0);
   std::iota(qo.begin(), qo.end(), 0);
   std::stable_sort(qo.begin(), qo.end(), [&](int a, int b) { return qc[a] > qc[b]; });
@@ -649,64 +601,20 @@ void order64(const exc_ctx* c, const std::vector<WorkItem>& it, const std::vecto
     tot += qc[q];
   }
   if (*std::max_element(load.begin(), load.end()) > 1.06 * tot / 8) {
-    for (int i : ord) out.push_back(it[i]);
+    for (const Item& x : ord) out.push_back(it[x.i]);
     return;
   }
-  std::vector<std::vector<int>> l(8);
-  for (int i : ord) l[qof[c->pairs[it[i].pair].q]].push_back(i);
-  size_t n = 0;
-  for (const auto& x : l) n = std::max(n, x.size());
+  size_t len[8] = {}, at[8], n = 0;
+  for (const Item& x : ord) n = std::max(n, ++len[qof[x.q]]);
   WorkItem none{};
   none.pair = -1;
-  for (size_t j = 0; j < n; ++j)
-    for (int b = 0; b < 8; ++b) out.push_back(j < l[b].size() ? it[l[b][j]] : none);
-}
-
-// The split with the smallest estimated time over the pairs [p0, p1): the longest-first schedule of its items (each
-// with a fixed overhead) on the CUs, whose matrix cores two workgroups share, plus half of the longest item where
-// there are more items than workgroup slots (costs are estimates, and a long item that starts late is waited for:
-// one k of the ZnO-like workload takes 7.6 ms with one item per part of a pair, 6.9 ms with the items of a few
-// passes that this picks), plus the traffic of the partial slots. At most max_slots items (0: no limit beyond 2 GiB of partials); the coarsest
-// split (one item per pair) always qualifies.
-Split64 pick_split64(const exc_ctx* c, int p0, int p1, size_t max_slots, int n_cu) {
-  Split64 best;
-  double best_t = 1e300;
-  const size_t slot_b = (size_t)c->gstride * 8;
-  if (!max_slots) max_slots = std::max<size_t>(p1 - p0, ((size_t)2 << 30) / slot_b);
-  std::vector<double> cs;
-  for (const Herk64K& k : kHerk64) {
-    if (k.nbt != c->nbt_max) continue;
-    const int npass = (c->n_occ + k.ng - 1) / k.ng;
-    for (int passes : {0, 4, 2, 1}) {
-      if (passes >= npass) continue;
-      for (int groups : {1, 2, 3, 4, 6, 0}) {
-        const Split64 sp{&k, passes, groups};
-        cs.clear();
-        for (int i = p0; i < p1 && cs.size() <= max_slots; ++i)
-          split_pair64(c, sp, c->pairs[i], [&](int, int, int, int, double x) { cs.push_back(x + 60.0); });
-        if (cs.size() > max_slots && !(passes == 0 && groups == 1)) continue;
-        double sum = 0.0, mx = 0.0, t;
-        for (double x : cs) { sum += x; mx = std::max(mx, x); }
-        if (cs.size() > (size_t)64 * n_cu) {
-          t = sum / n_cu + 0.5 * mx;
-        } else {
-          std::sort(cs.begin(), cs.end(), std::greater<double>());
-          std::priority_queue<double, std::vector<double>, std::greater<double>> h;
-          t = 0.0;
-          for (double x : cs) {
-            double at = 0.0;
-            if ((int)h.size() == n_cu) { at = h.top(); h.pop(); }
-            h.push(at + x);
-            t = std::max(t, at + x);
-          }
-          if (cs.size() > (size_t)n_cu * (k.nw == 4 ? 2 : 1)) t += 0.5 * mx;
-        }
-        t += (double)cs.size() * slot_b * 2 / 5e12 * 2.4e9 / 64;
-        if (t < 0.98 * best_t) { best_t = t; best = sp; }
-      }
-    }
+  for (int b = 0; b < 8; ++b) at[b] = out.size() + b;
+  out.resize(out.size() + 8 * n, none);
+  for (const Item& x : ord) {
+    size_t& p = at[qof[x.q]];
+    out[p] = it[x.i];
+    p += 8;
   }
-  return best;
 }
 
 // FP64 plan: `per` = 0 every pair in one launch, 1 one launch per k, 2 one launch per pair.
@@ -732,21 +640,34 @@ exc_status build_plan64(exc_ctx* c, Plan& P, int per, size_t max_slots) {
       if (c->pairs[i].nd > c->pairs[a].nd) a = i;
     b = a + 1;
   }
-  const Split64 sp = pick_split64(c, a, b, max_slots, n_cu);
-  if (!sp.k) return fail(c, EXC_EUNSUPPORTED, "no FP64 kernel for n_b = %d", c->nb_max);
-  P.h64 = sp.k;
+  const System64 sys{c->n_occ, c->n_s, c->n_chunk64, n_cu, (size_t)c->gstride * 8};
+  std::vector<Shape64> shapes;
+  for (const Herk64K& k : kHerk64) shapes.push_back(k.shape);
+  std::vector<int> nd;
+  for (int i = a; i < b; ++i) nd.push_back(c->pairs[i].nd);
+  const Split64 sp = pick_split64(sys, shapes, c->nbt_max, nd, max_slots);
+  if (sp.inst < 0) return fail(c, EXC_EUNSUPPORTED, "no FP64 kernel for n_b = %d", c->nb_max);
+  P.h64 = &kHerk64[sp.inst];
+  const Shape64& sh = P.h64->shape;
+  const int npass = (c->n_occ + sh.ng - 1) / sh.ng, step = sp.passes ? sp.passes : npass;
+  struct Run { int part0, part1; double cost; };
+  std::vector<Run> runs;
   std::vector<double> cost;
   std::vector<WorkItem> order;
   for (int k = 0; k < c->n_k; ++k) {
     for (int i = c->k_pair[k]; i < c->k_pair[k + 1]; ++i) {
-      split_pair64(c, sp, c->pairs[i], [&](int g0, int g1, int r0, int r1, double cs) {
-        WorkItem w{};
-        w.pair = i; w.g0 = g0; w.g1 = g1; w.ngc = sp.k->ng; w.rb0 = r0; w.rb1 = r1;
-        w.slot = (int)P.items.size();
-        P.items.push_back(w);
-        P.slot_w.push_back(c->pair_w[i]);
-        cost.push_back(cs);
-      });
+      runs.clear();
+      runs64(sys, sh, sp.groups, c->pairs[i].nd, [&](int r0, int r1, double cs) { runs.push_back({r0, r1, cs}); });
+      for (int g = 0; g < npass; g += step)
+        for (const Run& r : runs) {
+          const int n = std::min(step, npass - g);
+          WorkItem w{};
+          w.pair = i; w.g0 = g * sh.ng; w.g1 = std::min(c->n_occ, (g + n) * sh.ng); w.ngc = sh.ng; w.rb0 = r.part0; w.rb1 = r.part1;
+          w.slot = (int)P.items.size();
+          P.items.push_back(w);
+          P.slot_w.push_back(c->pair_w[i]);
+          cost.push_back(r.cost * n);
+        }
       P.pair_item.push_back((int)P.items.size());
       if (per == 2) {
         for (int j = P.pair_item[i]; j < P.pair_item[i + 1]; ++j) order.push_back(P.items[j]);
@@ -1066,7 +987,7 @@ void launch64(exc_ctx* c, const Plan& P, int i, int dtype, int k, Herk64Args& a,
   a.gstride = c->gstride;
   a.tmask = c->d_tmask;
   L.grid = dim3(a.n_items);
-  L.block = dim3(64 * P.h64->nw);
+  L.block = dim3(64 * P.h64->shape.nw);
   L.shmem = 0;
   L.fn = dtype == EXC_C64 ? (const void*)P.h64->fn64 : (const void*)P.h64->fn;
   L.arg = &a;
