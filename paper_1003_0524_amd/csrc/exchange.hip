@@ -228,6 +228,7 @@ struct exc_ctx {
   hipEvent_t ev_en = nullptr;         // end of the last energy call (its buffers are shared)
   bool ev_en_set = false;
   hipEvent_t ev_learn = nullptr;      // end of the last learned call (its buffers are shared)
+  bool learn_set = false;             // (it was asynchronous)
   int g_dtype = -1;
   // live kernel timing of the batched path: event-record nodes around the
   // sparse and tile kernels; one pool entry (3 events) per graph replay

@@ -156,29 +156,31 @@ exc_status learn_scratch(exc_ctx* c) {
   return EXC_OK;
 }
 
-// st after everything queued on the default stream so far (the context's own stream is non-blocking: nothing else
-// orders the two).
+// st after everything queued on the default stream so far (a non-blocking stream is not by itself).
 exc_status behind_default(exc_ctx* c, hipStream_t st) {
   HIPCHK(c, hipEventRecord(c->ev_in, nullptr));
   HIPCHK(c, hipStreamWaitEvent(st, c->ev_in, 0));
   return EXC_OK;
 }
 
-// The stream of a learned call: the caller's, or for NULL the context's own, behind the default stream if the arrays
-// are the device's (the call then ends in a wait for it, so that the default stream's later work finds the results).
-// The calls share the pointer tables, the scratch and the network's buffers: each is ordered after the last one,
+// The learned calls share the pointer tables, the scratch and the network's buffers: each is ordered after the last one,
 // whatever its stream. (A captured call cannot wait for an event from outside; one that writes tables is refused.)
-exc_status learn_begin(exc_ctx* c, void* stream, int on_device, hipStream_t* st) {
-  *st = stream ? (hipStream_t)stream : c->own;
-  if (!c->ev_learn) HIPCHK(c, hipEventCreateWithFlags(&c->ev_learn, hipEventDisableTiming));
-  else if (!capturing(*st)) HIPCHK(c, hipStreamWaitEvent(*st, c->ev_learn, 0));
-  return stream || !on_device ? EXC_OK : behind_default(c, *st);
+exc_status learn_begin(exc_ctx* c, hipStream_t st) {
+  if (c->learn_set && !capturing(st)) HIPCHK(c, hipStreamWaitEvent(st, c->ev_learn, 0));
+  return EXC_OK;
 }
 
-exc_status learn_end(exc_ctx* c, void* stream, hipStream_t st) {
+// The end of a call on st; one that returns its results (host arrays, or no stream given) waits for it.
+exc_status learn_end(exc_ctx* c, hipStream_t st, bool wait) {
   HIPCHK(c, hipGetLastError());
-  if (!capturing(st)) HIPCHK(c, hipEventRecord(c->ev_learn, st));
-  if (!stream) HIPCHK(c, hipStreamSynchronize(st));
+  if (wait) {
+    HIPCHK(c, hipStreamSynchronize(st));
+    c->learn_set = false;
+  } else if (!capturing(st)) {
+    if (!c->ev_learn) HIPCHK(c, hipEventCreateWithFlags(&c->ev_learn, hipEventDisableTiming));
+    HIPCHK(c, hipEventRecord(c->ev_learn, st));
+    c->learn_set = true;
+  }
   return EXC_OK;
 }
 
@@ -193,7 +195,7 @@ exc_status put_table(exc_ctx* c, void* dtab, const void* const* h, void* dtab1, 
       if (!x[k]) return fail(c, EXC_EINVAL, "pointer for k=%d is NULL", k);
   }
   if (capturing(st)) HIPCHK(c, hipStreamSynchronize(st));   // (not for capture)
-  if (st != c->own) TRY(behind_default(c, st));
+  if (st) TRY(behind_default(c, st));
   return put_pointers(c, c->n_k, (void**)dtab, h, (void**)dtab1, h1, st);
 }
 
@@ -260,8 +262,9 @@ exc_status exchange_nn_grad(exc_ctx* c, const float* X, const float* Y, int32_t 
   if (!X || !Y || !grad_out || n < 1) return fail(c, EXC_EINVAL, "X, Y, grad_out non-NULL and n >= 1 required");
   HIPCHK(c, hipSetDevice(c->device));
   TRY(nn_reserve(c, n));
-  hipStream_t st;
-  TRY(learn_begin(c, nullptr, on_device, &st));
+  hipStream_t st = c->own;
+  TRY(learn_begin(c, st));
+  if (on_device) TRY(behind_default(c, st));
   TRY(nn_stage(c, s->X, X, (size_t)n * s->I, on_device, st));
   TRY(nn_stage(c, s->T, Y, (size_t)n * s->O, on_device, st));
   nn_backward(s, st, n, 0);
@@ -283,8 +286,9 @@ exc_status exchange_nn_train(exc_ctx* c, const float* X, const float* Y, int32_t
     return fail(c, EXC_EINVAL, "X, Y non-NULL, n >= 1, epochs >= 0 and lr > 0 required");
   HIPCHK(c, hipSetDevice(c->device));
   TRY(nn_reserve(c, n));
-  hipStream_t st;
-  TRY(learn_begin(c, nullptr, on_device, &st));
+  hipStream_t st = c->own;
+  TRY(learn_begin(c, st));
+  if (on_device) TRY(behind_default(c, st));
   TRY(nn_stage(c, s->X, X, (size_t)n * s->I, on_device, st));
   TRY(nn_stage(c, s->T, Y, (size_t)n * s->O, on_device, st));
   if (epochs > 0 && (!s->gexec || s->g_n != n || s->g_lr != lr)) {
@@ -320,17 +324,17 @@ exc_status exchange_nn_predict(exc_ctx* c, const float* X, int32_t n, float* Y_o
   if (!X || !Y_out || n < 1) return fail(c, EXC_EINVAL, "X, Y_out non-NULL and n >= 1 required");
   HIPCHK(c, hipSetDevice(c->device));
   TRY(nn_reserve(c, n));
-  hipStream_t st;
-  TRY(learn_begin(c, stream, on_device, &st));
-  if (stream) HIPCHK(c, hipStreamSynchronize(c->own));   // a training run may still use the buffers
+  hipStream_t st = stream || on_device ? (hipStream_t)stream : c->own;
+  TRY(learn_begin(c, st));
+  if (st != c->own) HIPCHK(c, hipStreamSynchronize(c->own));   // a training run may still use the buffers
   if (on_device) {
     nn_forward(s, st, X, n, Y_out);
-    return learn_end(c, stream, st);
+    return learn_end(c, st, !stream);
   }
   TRY(nn_stage(c, s->X, X, (size_t)n * s->I, 0, st));
   nn_forward(s, st, s->X, n, s->y);
   HIPCHK(c, hipMemcpyAsync(Y_out, s->y, (size_t)n * s->O * sizeof(float), hipMemcpyDeviceToHost, st));
-  return learn_end(c, nullptr, st);
+  return learn_end(c, st, true);
 }
 
 exc_status exchange_nn_features(exc_ctx* c, const double* P_new, const double* P_old, int64_t n_real,
@@ -341,8 +345,8 @@ exc_status exchange_nn_features(exc_ctx* c, const double* P_new, const double* P
   HIPCHK(c, hipSetDevice(c->device));
   TRY(learn_scratch(c));
   LearnScratch* l = c->ls;
-  hipStream_t st;
-  TRY(learn_begin(c, stream, 1, &st));
+  hipStream_t st = (hipStream_t)stream;
+  TRY(learn_begin(c, st));
   const long nchunk = (long)((n_real + SK_CHUNK - 1) / SK_CHUNK);
   const size_t need = (size_t)nchunk * (m + 1);
   if (need > l->part_n) {
@@ -356,7 +360,7 @@ exc_status exchange_nn_features(exc_ctx* c, const double* P_new, const double* P
   hipLaunchKernelGGL(nn_sketch_partial, dim3((unsigned)nchunk), dim3(256), 0, st, P_new, P_old, (long)n_real, m,
                      seed, l->part);
   hipLaunchKernelGGL(nn_sketch_final, dim3(m), dim3(256), 0, st, l->part, (int)nchunk, m, x_out, norm_out);
-  return learn_end(c, stream, st);
+  return learn_end(c, st, !stream);
 }
 
 exc_status exchange_eigh(exc_ctx* c, const void* const* A_k, double* w_out, void* Z_out, void* stream) {
@@ -366,13 +370,13 @@ exc_status exchange_eigh(exc_ctx* c, const void* const* A_k, double* w_out, void
   HIPCHK(c, hipSetDevice(c->device));
   TRY(learn_scratch(c));
   LearnScratch* l = c->ls;
-  hipStream_t st;
-  TRY(learn_begin(c, stream, 1, &st));
+  hipStream_t st = (hipStream_t)stream;
+  TRY(learn_begin(c, st));
   TRY(put_table(c, (void*)l->tabA, A_k, nullptr, nullptr, st));
   EighArgs a{(const double2* const*)l->tabA, c->d_knb, l->work, (double2*)Z_out, l->z_off, w_out, l->w_off,
              l->sweeps};
   hipLaunchKernelGGL(eigh_jacobi, dim3(c->n_k), dim3(256), 0, st, a);
-  return learn_end(c, stream, st);
+  return learn_end(c, st, !stream);
 }
 
 exc_status exchange_nn_project(exc_ctx* c, const void* const* Va_k, const void* const* Vb_k, const void* Z,
@@ -387,14 +391,14 @@ exc_status exchange_nn_project(exc_ctx* c, const void* const* Va_k, const void* 
   HIPCHK(c, hipSetDevice(c->device));
   TRY(learn_scratch(c));
   LearnScratch* l = c->ls;
-  hipStream_t st;
-  TRY(learn_begin(c, stream, 1, &st));
+  hipStream_t st = (hipStream_t)stream;
+  TRY(learn_begin(c, st));
   TRY(put_table(c, (void*)l->tabA, Va_k, (void*)l->tabB, Vb_k, st));
   ProjArgs a{(const double2* const*)l->tabA, (const double2* const*)l->tabB, (const double2*)Z, l->z_off,
              c->d_knb, n_blk, scale, y_out, nullptr, nullptr};
   const size_t lds = (size_t)c->nb_max * n_blk * sizeof(double2);
   hipLaunchKernelGGL(nn_project, dim3(c->n_k), dim3(256), lds, st, a);
-  return learn_end(c, stream, st);
+  return learn_end(c, st, !stream);
 }
 
 exc_status exchange_nn_expand(exc_ctx* c, const void* const* Vanchor_k, const void* Z, int32_t n_blk,
@@ -409,14 +413,14 @@ exc_status exchange_nn_expand(exc_ctx* c, const void* const* Vanchor_k, const vo
   HIPCHK(c, hipSetDevice(c->device));
   TRY(learn_scratch(c));
   LearnScratch* l = c->ls;
-  hipStream_t st;
-  TRY(learn_begin(c, stream, 1, &st));
+  hipStream_t st = (hipStream_t)stream;
+  TRY(learn_begin(c, st));
   TRY(put_table(c, (void*)l->tabA, Vanchor_k, (void*)l->tabC, (const void* const*)Vout_k, st));
   ProjArgs a{nullptr, nullptr, (const double2*)Z, l->z_off, c->d_knb, n_blk, scale, const_cast<float*>(y),
              (const double2* const*)l->tabA, (double2* const*)l->tabC};
   const size_t lds = (size_t)((n_blk * (n_blk + 1) + 3) / 4) * 16 + (size_t)8 * n_blk * sizeof(double2);
   hipLaunchKernelGGL(nn_expand, dim3(c->n_k, (c->nb_max + 3) / 4), dim3(256), lds, st, a);
-  return learn_end(c, stream, st);
+  return learn_end(c, st, !stream);
 }
 
 }  // extern "C"
