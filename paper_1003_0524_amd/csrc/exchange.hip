@@ -629,24 +629,22 @@ exc_status build_plan64(exc_ctx* c, Plan& P, int per, size_t max_slots) {
   P.slot_w.clear();
   P.order_begin.assign(1, 0);
   // the split is chosen for all pairs, the k with the most pairs, or the largest pair
-  int a = 0, b = (int)c->pairs.size();
-  if (per == 1) {
-    int km = 0;
-    for (int k = 1; k < c->n_k; ++k)
-      if (c->k_pair[k + 1] - c->k_pair[k] > c->k_pair[km + 1] - c->k_pair[km]) km = k;
-    a = c->k_pair[km];
-    b = c->k_pair[km + 1];
-  } else if (per == 2) {
-    for (int i = 1; i < b; ++i)
-      if (c->pairs[i].nd > c->pairs[a].nd) a = i;
-    b = a + 1;
+  std::vector<std::vector<int>> nd;
+  int at = 0;
+  if (per == 0) nd.resize(1);
+  for (int k = 0; k < c->n_k; ++k) {
+    if (per == 1) nd.push_back({});
+    for (int i = c->k_pair[k]; i < c->k_pair[k + 1]; ++i) {
+      if (per == 2) nd.push_back({});
+      nd.back().push_back(c->pairs[i].nd);
+      if (per == 2 && nd.back()[0] > nd[at][0]) at = i;
+    }
+    if (per == 1 && nd.back().size() > nd[at].size()) at = k;
   }
   const System64 sys{c->n_occ, c->n_s, c->n_chunk64, n_cu, (size_t)c->gstride * 8};
   std::vector<Shape64> shapes;
   for (const Herk64K& k : kHerk64) shapes.push_back(k.shape);
-  std::vector<int> nd;
-  for (int i = a; i < b; ++i) nd.push_back(c->pairs[i].nd);
-  const Split64 sp = pick_split64(sys, shapes, c->nbt_max, nd, max_slots);
+  const Split64 sp = pick_split64(sys, shapes, c->nbt_max, nd, at, max_slots);
   if (sp.inst < 0) return fail(c, EXC_EUNSUPPORTED, "no FP64 kernel for n_b = %d", c->nb_max);
   P.h64 = &kHerk64[sp.inst];
   const Shape64& sh = P.h64->shape;

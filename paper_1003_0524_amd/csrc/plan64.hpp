@@ -60,27 +60,46 @@ void runs64(const System64& c, const Shape64& k, int groups, int nd, F&& push) {
 // items (each with a fixed overhead) on the CUs, whose matrix cores two workgroups share, plus half of the longest item
 // where there are more items than workgroup slots (costs are estimates, and a long item that starts late is waited for:
 // one k of the ZnO-like workload takes 7.6 ms with one item per part of a pair, 6.9 ms with the items of a few
-// passes that this picks), plus the traffic of the partial slots. At most max_slots items (0: no limit beyond 2 GiB of
-// partials); the coarsest split (one item per pair) always qualifies.
+// passes that this picks), plus the traffic of the partial slots. `launches` are the dense rows of the pairs of each launch
+// of the plan; the time is that of launch `at`, but every launch keeps to max_slots items (0: 2 GiB of partials), unless it
+// has more pairs than that (no split would do). The coarsest split (one item per pair) always qualifies.
 //
 // Pairs of the same nd have the same items, and a split whose schedule cannot be shorter than the best so far (work over
 // CUs, longest item) needs none: 288 pairs of 144 different nd 11.5 -> 3.1 ms, 4096 small pairs 17 -> 0.3 ms against
 // every item listed, sorted and scheduled for every split.
-inline Split64 pick_split64(const System64& c, const std::vector<Shape64>& shapes, int nbt, std::vector<int> nd,
-                            size_t max_slots) {
+inline Split64 pick_split64(const System64& c, const std::vector<Shape64>& shapes, int nbt,
+                            const std::vector<std::vector<int>>& launches, int at, size_t max_slots) {
   struct Group { double cost; size_t n; };               // n items of a cost
   static const int kGroups[6] = {1, 2, 3, 4, 6, 0}, kPasses[4] = {0, 4, 2, 1};
   Split64 best;
   double best_t = 1e300;
   const size_t n_cu = (size_t)c.n_cu;
-  if (!max_slots) max_slots = std::max(nd.size(), ((size_t)2 << 30) / c.slot_bytes);
+  if (!max_slots) max_slots = ((size_t)2 << 30) / c.slot_bytes;
+  std::vector<int> nd(launches[at]);
   std::sort(nd.begin(), nd.end());
+  std::vector<int> sizes;                                // every nd
+  for (const auto& l : launches) sizes.insert(sizes.end(), l.begin(), l.end());
+  std::sort(sizes.begin(), sizes.end());
+  sizes.erase(std::unique(sizes.begin(), sizes.end()), sizes.end());
+  std::vector<size_t> parts(sizes.back() + 1);           // runs of a pair of nd dense rows under one grouping
   std::vector<Group> runs[6], items;
+  size_t most[6];                                        // most items of a launch in one run of passes
   std::vector<double> h;
   for (int i = 0; i < (int)shapes.size(); ++i) {
     const Shape64& k = shapes[i];
     if (k.nbt != nbt) continue;
     for (int g = 0; g < 6; ++g) {
+      for (int x : sizes) {
+        parts[x] = 0;
+        runs64(c, k, kGroups[g], x, [&](int, int, double) { ++parts[x]; });
+      }
+      most[g] = 0;
+      for (const auto& l : launches) {
+        if (l.size() > max_slots && &l != &launches[at]) continue;
+        size_t n = 0;
+        for (int x : l) n += parts[x];
+        most[g] = std::max(most[g], n);
+      }
       runs[g].clear();
       for (size_t a = 0, b; a < nd.size(); a = b) {
         b = std::upper_bound(nd.begin() + a, nd.end(), nd[a]) - nd.begin();
@@ -104,7 +123,7 @@ inline Split64 pick_split64(const System64& c, const std::vector<Shape64>& shape
           sum += x.cost * x.n;
           mx = std::max(mx, x.cost);
         }
-        if (n > max_slots && !(passes == 0 && kGroups[g] == 1)) continue;
+        if (most[g] * ((npass + per - 1) / per) > max_slots && !(passes == 0 && kGroups[g] == 1)) continue;
         const bool many = n > 64 * n_cu;
         const double extra = (many || n > n_cu * (k.nw == 4 ? 2 : 1) ? 0.5 * mx : 0.0) +
                              (double)n * c.slot_bytes * 2 / 5e12 * 2.4e9 / 64;
@@ -116,16 +135,16 @@ inline Split64 pick_split64(const System64& c, const std::vector<Shape64>& shape
           t = 0.0;
           for (const Group& x : items)
             for (size_t u = 0; u < x.n; ++u) {
-              const double at = h[0] + x.cost;
-              t = std::max(t, at);
+              const double end = h[0] + x.cost;
+              t = std::max(t, end);
               size_t p = 0;
               for (size_t q = 1; q < n_cu; q = 2 * p + 1) {
                 if (q + 1 < n_cu && h[q + 1] < h[q]) ++q;
-                if (h[q] >= at) break;
+                if (h[q] >= end) break;
                 h[p] = h[q];
                 p = q;
               }
-              h[p] = at;
+              h[p] = end;
             }
         }
         t += extra;

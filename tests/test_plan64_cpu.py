@@ -1,5 +1,6 @@
 """The planner of the FP64 Cholesky/HERK kernel (plan64.hpp, host code) against its plain form, which lists, sorts and
-schedules every item of every split: the same choice at a fraction of the time. Built with the host compiler.
+schedules every item of every split: the same choice at a fraction of the time. And its limit on the items of a launch, for
+every launch of a plan and not only the one that the split is chosen for. Built with the host compiler.
 """
 import os
 import random
@@ -65,7 +66,9 @@ static Split64 plain(const System64& c, const std::vector<Shape64>& sh, int nbt,
   }
   return best;
 }
-// each line: nbt n_occ n_s n_chunk max_slots pairs nd...; out: the two choices, items of each, microseconds of each
+// each line: nbt n_occ n_s n_chunk max_slots pairs nd... launches (pairs nd...)...: the split is chosen for the first ones,
+// the launches after them keep to the limit too; out: the two choices and the items of each (the plain form sees the first
+// launch only), microseconds of each, items of the further launches under the plain choice and under the planner's
 int main() {
   std::vector<Shape64> sh;
   for (auto& x : (int[][2]){INSTANCES}) sh.push_back(shape(x[0], x[1]));
@@ -74,19 +77,35 @@ int main() {
   while (scanf("%d %d %d %d %zu %d", &nbt, &n_occ, &n_s, &n_chunk, &max, &pairs) == 6) {
     std::vector<int> nd(pairs);
     for (int& x : nd) if (scanf("%d", &x) != 1) return 1;
+    std::vector<std::vector<int>> all(1, nd);
+    int more;
+    if (scanf("%d", &more) != 1) return 1;
+    for (int l = 0; l < more; ++l) {
+      int n;
+      if (scanf("%d", &n) != 1) return 1;
+      all.push_back(std::vector<int>(n));
+      for (int& x : all.back()) if (scanf("%d", &x) != 1) return 1;
+    }
     const System64 c{n_occ, n_s, n_chunk, 256, (size_t)nbt * (nbt + 1) / 2 * 2048};
     const auto a = std::chrono::steady_clock::now();
     const Split64 p = plain(c, sh, nbt, nd, max);
     const auto b = std::chrono::steady_clock::now();
-    const Split64 q = pick_split64(c, sh, nbt, nd, max);
+    const Split64 q = pick_split64(c, sh, nbt, all, 0, max);
     const auto e = std::chrono::steady_clock::now();
     for (const Split64& s : {p, q}) {
       size_t n = 0;
       for (int x : nd) items(c, sh[s.inst], s.passes, s.groups, x, [&](double) { ++n; });
       printf("%d %d %d %zu ", sh[s.inst].ng, s.passes, s.groups, n);
     }
-    printf("%.1f %.1f\n", std::chrono::duration<double, std::micro>(b - a).count(),
+    printf("%.1f %.1f", std::chrono::duration<double, std::micro>(b - a).count(),
            std::chrono::duration<double, std::micro>(e - b).count());
+    for (const Split64& s : {p, q})
+      for (int l = 1; l <= more; ++l) {
+        size_t n = 0;
+        for (int x : all[l]) items(c, sh[s.inst], s.passes, s.groups, x, [&](double) { ++n; });
+        printf(" %zu", n);
+      }
+    printf("\n");
   }
 }
 """
@@ -106,11 +125,16 @@ def planner(tmp_path_factory):
     subprocess.run([cxx, "-O2", "-std=c++17", "-I", CSRC, str(src), "-o", str(d / "plan")], check=True)
 
     def run(cases):
-        text = "\n".join(" ".join(map(str, [*c[:5], len(c[5]), *c[5]])) for c in cases)
+        def line(c):
+            more = c[6] if len(c) > 6 else []
+            return [*c[:5], len(c[5]), *c[5], len(more), *(x for l in more for x in [len(l), *l])]
+
+        text = "\n".join(" ".join(map(str, line(c))) for c in cases)
         out = subprocess.run([str(d / "plan")], input=text, capture_output=True, text=True, check=True, timeout=300)
         rows = [r.split() for r in out.stdout.splitlines()]
         assert len(rows) == len(cases)
-        return [([int(x) for x in r[:4]], [int(x) for x in r[4:8]], float(r[8]), float(r[9])) for r in rows]
+        return [([int(x) for x in r[:4]], [int(x) for x in r[4:8]], float(r[8]), float(r[9]), [int(x) for x in r[10:]])
+                for r in rows]
 
     return run
 
@@ -132,7 +156,7 @@ def _random_cases():
 
 
 def test_same_choice_as_the_plain_form(planner):
-    for case, (p, q, _, _) in zip(cases := _random_cases(), planner(cases)):
+    for case, (p, q, *_) in zip(cases := _random_cases(), planner(cases)):
         assert p == q, (case, p, q)
 
 
@@ -147,3 +171,21 @@ def test_a_fraction_of_its_time(planner):
     old, new = sum(r[2] for r in rows), sum(r[3] for r in rows)
     print(f"[plan64] plain {old:.0f} us, pick_split64 {new:.0f} us")
     assert new < old / 3, (old, new)
+
+
+def test_every_launch_keeps_to_the_limit(planner):
+    """Two k of a subset each: fewer but larger pairs in the second one, whose items follow the split chosen for the first."""
+    rng = random.Random(9)
+    cases = [(16, 3, 0, 0, 240, [640] * 7, [[1739] * 5]), (8, 2, 0, 0, 903, [448] * 34, [[1251] * 29]),
+             (5, 2, 0, 0, 2161, [576] * 89, [[1592] * 59, [100] * 80])]
+    for _ in range(60):
+        n = rng.randint(2, 60)
+        lo = 64 * rng.randint(1, 10)
+        more = [_nd(rng, rng.randint(1, n), lo, lo + rng.randint(0, 1200)) for _ in range(rng.randint(1, 4))]
+        cases.append((rng.randint(1, 16), rng.randint(1, 20), 0, 0, n + rng.randint(0, 2000), [lo] * n, more))
+    over = 0
+    for case, (p, q, _, _, items) in zip(cases, planner(cases)):
+        n = len(case[6])
+        assert q[3] <= case[4] and max(items[n:]) <= case[4], (case, q, items)
+        over += max(items[:n]) > case[4]
+    assert over >= 3                     # (the split of the first launch alone exceeds the limit in the others)
