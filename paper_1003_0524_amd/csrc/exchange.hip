@@ -653,6 +653,12 @@ exc_status build_plan64(exc_ctx* c, Plan& P, int per, size_t max_slots) {
   std::vector<Run> runs;
   std::vector<double> cost;
   std::vector<WorkItem> order;
+  const size_t most = c->pairs.size() * ((npass + step - 1) / step) *
+                      (sp.groups ? sp.groups : 1 + (*std::max_element(c->nd.begin(), c->nd.end()) + 63) / 64);
+  P.items.reserve(most);
+  P.slot_w.reserve(most);
+  cost.reserve(most);
+  order.reserve(most);
   for (int k = 0; k < c->n_k; ++k) {
     for (int i = c->k_pair[k]; i < c->k_pair[k + 1]; ++i) {
       runs.clear();
@@ -676,7 +682,19 @@ exc_status build_plan64(exc_ctx* c, Plan& P, int per, size_t max_slots) {
     P.k_item.push_back((int)P.items.size());
     P.slot_begin.push_back((int)P.items.size());
     if (per == 1) {
-      order64(c, P.items, cost, P.k_item[k], P.k_item[k + 1], order);
+      // (as a rule every k has the same q: the order of the k before it)
+      const int p0 = c->k_pair[k], np = c->k_pair[k + 1] - p0, ni = P.k_item[k + 1] - P.k_item[k];
+      bool same = k > 0 && p0 - c->k_pair[k - 1] == np;
+      for (int i = p0; same && i < p0 + np; ++i) same = c->pairs[i].q == c->pairs[i - np].q;
+      if (same) {
+        for (int j = P.order_begin[k - 1]; j < P.order_begin[k]; ++j) {
+          WorkItem w = order[j];
+          if (w.pair >= 0) { w.pair += np; w.slot += ni; }
+          order.push_back(w);
+        }
+      } else {
+        order64(c, P.items, cost, P.k_item[k], P.k_item[k + 1], order);
+      }
       P.order_begin.push_back((int)order.size());
     }
   }
