@@ -347,7 +347,9 @@ exc_status exchange_query(const exc_ctx *ctx, int32_t what, double *value);
  * instance (EXC_FUSED_SPLIT=1: an item per n'' chunk) and EXC_FUSED=0 the
  * block-sparse + tile path (neither is then tuned; FP64: the block-sparse rows in a
  * kernel of their own); EXC_SPARSE_NCW=1|2|4 fixes the
- * columns each wavefront of the block-sparse kernel takes (HERK form); EXC_GRAPH=1
+ * columns each wavefront of the block-sparse kernel takes (HERK form);
+ * EXC_HERK64=<id>,<passes>,<groups> fixes the FP64 kernel's instance (what = 3), n'' passes
+ * per item (0: all) and runs of row parts per pair (0: a part each); EXC_GRAPH=1
  * replays the batched launch from a HIP graph instead of enqueueing its kernels.
  */
 

@@ -644,7 +644,14 @@ exc_status build_plan64(exc_ctx* c, Plan& P, int per, size_t max_slots) {
   const System64 sys{c->n_occ, c->n_s, c->n_chunk64, n_cu, (size_t)c->gstride * 8};
   std::vector<Shape64> shapes;
   for (const Herk64K& k : kHerk64) shapes.push_back(k.shape);
-  const Split64 sp = pick_split64(sys, shapes, c->nbt_max, nd, at, max_slots);
+  Split64 sp;
+  if (const char* ev = getenv("EXC_HERK64")) {           // a fixed instance and split (tests): id,passes,groups
+    int id = 0, passes = 1, groups = 1;
+    if (sscanf(ev, "%d,%d,%d", &id, &passes, &groups) == 3 && passes >= 0 && groups >= 0)
+      for (int i = 0; i < kNumHerk64; ++i)
+        if (kHerk64[i].id() == id && kHerk64[i].shape.nbt == c->nbt_max) sp = Split64{i, passes, groups};
+  }
+  if (sp.inst < 0) sp = pick_split64(sys, shapes, c->nbt_max, nd, at, max_slots);
   if (sp.inst < 0) return fail(c, EXC_EUNSUPPORTED, "no FP64 kernel for n_b = %d", c->nb_max);
   P.h64 = &kHerk64[sp.inst];
   const Shape64& sh = P.h64->shape;

@@ -231,11 +231,15 @@ __global__ __launch_bounds__((256 * Herk64Cfg<NBT, NG, C64>::NWC), 2) void herk6
       const int q = uni(pi.q);
       const double2 *coef = a.coef + q * a.coef_qs, *cvec = a.cvec + q * a.cvec_qs;
       const auto rs = make_rsrc(mbase + (long)gbase * nb * nmb * ESZ, (uint32_t)((long)ng * nb * nmb * ESZ));
-      uint32_t co[CTW];                                // this lane's column of each tile
+      // this lane's column of each tile, no column: past every resource also with a row's offset added (0xFFFFFFF0
+      // would wrap around to the first columns)
+      constexpr uint32_t NOCOL = 0xFFFFFF00u;
+      static_assert((kH64Rows - 1) * 16 <= 0xF0, "NOCOL with a row's offset");
+      uint32_t co[CTW];
 #pragma unroll
       for (int j = 0; j < CTW; ++j) {
         const int ct = wc * CTW + j, g = ct / NBT, n = (ct - g * NBT) * 8 + c8;
-        co[j] = g < ng && n < nb ? (uint32_t)((g * nb + n) * nmb * ESZ) : OOB;
+        co[j] = g < ng && n < nb ? (uint32_t)((g * nb + n) * nmb * ESZ) : NOCOL;
       }
       // A load brings rows 8 i + 2 lq + part of the chunk (i = 0, 1): a lane holds one of the two rows that the
       // lanes of its column contract in steps 2 i and 2 i + 1 and gets the other one from its neighbour
