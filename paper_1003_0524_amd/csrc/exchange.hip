@@ -42,8 +42,8 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kScratchDevices] = {};
 
-// Device buffers that replace the context's own for one no-allocation call (see ScratchView
-// users: ws_base, tile_args, sparse_args, fused_args, cfg_sparse, cfg_reduce).
+// Device buffers that replace the context's own for one call, of the no-allocation entry point or with shared FP64 slots
+// (see ScratchView users: ws_base, tile_args, sparse_args, fused_args, cfg_sparse, cfg_reduce).
 struct ScratchView {
   void* ws;          // workspace of the call's k, shifted by the k's first element
   double* dsp;       // FP64 |Y_s|^2 sums, shifted by the k's first pair
@@ -178,6 +178,10 @@ struct exc_ctx {
   double* d_pair_w = nullptr;
   int32_t* d_pair_begin = nullptr;
   Plan plain, bat, perk;              // perk: FP64 HERK, one launch per k (bat when there is one k)
+  Plan capt;                          // FP64 HERK with part_shared: of captured calls, slots from part_slots on
+  bool part_shared = false;           // every k of perk has the first part_slots slots, in turn
+  size_t part_slots = 0;
+  hipEvent_t ev_part = nullptr;       //  their last use
   bool h64 = false;                   // FP64 Cholesky/HERK through herk64_kernel
   Chunk64* d_chunk64 = nullptr;          // its chunks of block-sparse rows (complex128 M); none: sparse_kernel first
   int n_chunk64 = 0;
@@ -201,7 +205,7 @@ struct exc_ctx {
   double* d_dsp = nullptr;
   void* d_gpart = nullptr;
   double* d_dpart = nullptr;
-  const ScratchView* sv = nullptr;    // set only during exchange_matrix_noalloc
+  const ScratchView* sv = nullptr;    // set only during a call on other buffers than the context's
   int gstride = 0, dstride = 0;
   double2* d_vres = nullptr;
   std::vector<int64_t> v_off;
@@ -376,6 +380,7 @@ void release(exc_ctx* c) {
   if (c->ev_in) hipEventDestroy(c->ev_in);
   if (c->ev_tab) hipEventDestroy(c->ev_tab);
   if (c->ev_chunk) hipEventDestroy(c->ev_chunk);
+  if (c->ev_part) hipEventDestroy(c->ev_part);
   free_chunk_plans(c);
   if (c->ev_en) hipEventDestroy(c->ev_en);
   if (c->ev_learn) hipEventDestroy(c->ev_learn);
@@ -386,7 +391,7 @@ void release(exc_ctx* c) {
   c->ev_g[0] = c->ev_g[1] = nullptr;
   for (hipEvent_t& e : c->ev_bt) if (e) hipEventDestroy(e);
   c->ev_bt[0] = c->ev_bt[1] = nullptr;
-  c->ev_in = c->ev_out = c->ev_tab = c->ev_chunk = nullptr;
+  c->ev_in = c->ev_out = c->ev_tab = c->ev_chunk = c->ev_part = nullptr;
   c->own = nullptr;
   void* ptrs[] = {c->d_coef, c->d_cvec, c->d_schur, c->d_U, c->d_row_chan, c->d_ch_off,
                   c->d_ch_len, c->d_ch_coef, c->d_rowinfo, c->d_runs, c->d_coefpad, c->d_schunk, c->d_sgroup, c->d_units, c->d_ucount, c->d_uowner, c->d_uw, c->d_chunk64, c->d_pairs, c->d_pair_w, c->d_pair_begin,
@@ -398,6 +403,7 @@ void release(exc_ctx* c) {
   free_plan(c->plain);
   free_plan(c->bat);
   free_plan(c->perk);
+  free_plan(c->capt);
 }
 
 // Dense rows per row block of a fused or wide instance (its row parts when items are
@@ -618,8 +624,9 @@ void order64(const exc_ctx* c, const std::vector<WorkItem>& it, const std::vecto
   }
 }
 
-// FP64 plan: `per` = 0 every pair in one launch, 1 one launch per k, 2 one launch per pair.
-exc_status build_plan64(exc_ctx* c, Plan& P, int per, size_t max_slots) {
+// FP64 plan: `per` = 0 every pair in one launch, 1 one launch per k, 2 one launch per pair. At most max_slots items a
+// launch and total_slots in all (see pick_split64).
+exc_status build_plan64(exc_ctx* c, Plan& P, int per, size_t max_slots, size_t total_slots) {
   int n_cu = 256;
   (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device);
   P.items.clear();
@@ -651,7 +658,7 @@ exc_status build_plan64(exc_ctx* c, Plan& P, int per, size_t max_slots) {
       for (int i = 0; i < kNumHerk64; ++i)
         if (kHerk64[i].id() == id && kHerk64[i].shape.nbt == c->nbt_max) sp = Split64{i, passes, groups};
   }
-  if (sp.inst < 0) sp = pick_split64(sys, shapes, c->nbt_max, nd, at, max_slots);
+  if (sp.inst < 0) sp = pick_split64(sys, shapes, c->nbt_max, nd, at, max_slots, total_slots);
   if (sp.inst < 0) return fail(c, EXC_EUNSUPPORTED, "no FP64 kernel for n_b = %d", c->nb_max);
   P.h64 = &kHerk64[sp.inst];
   const Shape64& sh = P.h64->shape;
@@ -1196,6 +1203,23 @@ exc_status launch_chunks(exc_ctx* c, const ChunkPlan& P, const Plan& plan, int d
 exc_status run_k_batched(exc_ctx* c, int k, int dtype, hipStream_t st) {
   if (needs_ws(c)) TRY(ensure_ws(c, c->ws_k_bytes));
   const int p0 = c->k_pair[k], p1 = c->k_pair[k + 1];
+  if (c->part_shared) {                              // (FP64) this call's slots
+    const bool cap = capturing(st);
+    const Plan& P = cap ? c->capt : c->perk;
+    const size_t slot_b = (size_t)c->gstride * 8;
+    ScratchView v{};
+    v.ws = ws_base(c, k);
+    v.gpart = (void*)((uintptr_t)c->d_gpart + (cap ? c->part_slots * slot_b : -(uintptr_t)P.slot_begin[k] * slot_b));
+    v.dpart = c->d_dpart;
+    if (!cap) HIPCHK(c, hipStreamWaitEvent(st, c->ev_part, 0));
+    c->sv = &v;
+    launch_sparse(c, dtype, k, p0, p1 - p0, st);
+    launch_k(c, P, dtype, k, st);
+    launch_reduce(c, P, k, 1, st);
+    c->sv = nullptr;
+    if (!cap) HIPCHK(c, hipEventRecord(c->ev_part, st));
+    return EXC_OK;
+  }
   launch_sparse(c, dtype, k, p0, p1 - p0, st);
   const Plan& P = k_plan(c);
   ChunkPlan* cp = nullptr;
@@ -1390,6 +1414,56 @@ size_t noalloc_slots(const exc_ctx* c) {
   return most;
 }
 
+// FP64 HERK: the plans of the context's path; `coarse`: one item per pair.
+//
+// A launch of one k is split finely enough to fill the GPU by itself. With slots of its own for every k, calls on
+// different streams do not meet, but over many k the slots add up: 20 k of 216 SrTiO3-like pairs to 16 GB where one item
+// per pair takes 0.8 GB. Past kPartialBytes all k use the same slots and their calls follow each other; captured calls,
+// whose replays nothing orders, then keep to one item per pair in slots of their own. (Coarser items for every k instead:
+// 64 k of the ZnO-like system within 4 GiB 11.8 ms a k, with shared slots 6.5.) One launch per pair: past kPartialBytes no
+// more slots than items of one 64-row block and up to 12 (8) band tiles of n'' take.
+constexpr size_t kPartialBytes = (size_t)2 << 30;
+exc_status build_plans64(exc_ctx* c, bool coarse) {
+  free_plan(c->plain);
+  free_plan(c->bat);
+  free_plan(c->perk);
+  free_plan(c->capt);
+  c->part_shared = false;
+  if (!c->batched) {
+    const int nbt = c->nbt_max, ng = std::max(1, nbt <= 3 ? 12 / nbt : 8 / nbt);
+    size_t total = 0, room = kPartialBytes / ((size_t)c->gstride * 8);
+    for (const PairInfo& p : c->pairs) total += (size_t)((c->n_occ + ng - 1) / ng) * (p.nsb + p.ndb);
+    return build_plan64(c, c->plain, 2, coarse ? 1 : 0, std::max(total, room));
+  }
+  const size_t lim = coarse ? 1 : noalloc_slots(c);
+  TRY(build_plan64(c, c->bat, 0, c->n_k == 1 || coarse ? lim : 0, 0));
+  if (c->n_k == 1) return EXC_OK;
+  TRY(build_plan64(c, c->perk, 1, lim, 0));
+  if (coarse || (size_t)c->perk.n_slots * c->gstride * 8 <= kPartialBytes) return EXC_OK;
+  c->part_shared = true;
+  c->part_slots = 0;
+  for (int k = 0; k < c->n_k; ++k)
+    c->part_slots = std::max(c->part_slots, (size_t)(c->perk.slot_begin[k + 1] - c->perk.slot_begin[k]));
+  if (!c->ev_part) HIPCHK(c, hipEventCreateWithFlags(&c->ev_part, hipEventDisableTiming));
+  return build_plan64(c, c->capt, 1, 1, 0);
+}
+
+// The partial slots of the context's plans.
+exc_status alloc_partials(exc_ctx* c) {
+  const size_t perk = c->part_shared ? c->part_slots + c->capt.n_slots : c->perk.n_slots;
+  const size_t nslot = std::max({(size_t)c->plain.n_slots, (size_t)c->bat.n_slots, perk});
+  const size_t asz = c->precision == EXC_FP64 ? 8 : 4;
+  hipFree(c->d_gpart);
+  hipFree(c->d_dpart);
+  c->d_gpart = nullptr;
+  c->d_dpart = nullptr;
+  TRY(dalloc(c, (char**)&c->d_gpart, nslot * c->gstride * asz));
+  TRY(dalloc(c, &c->d_dpart, nslot * (size_t)c->dstride));
+  HIPCHK(c, hipMemset(c->d_gpart, 0, nslot * c->gstride * asz));
+  HIPCHK(c, hipMemset(c->d_dpart, 0, nslot * (size_t)c->dstride * 8));
+  return EXC_OK;
+}
+
 // Switch the context to a main-kernel configuration: a fused instance, or
 // (f == nullptr) the block-sparse + tile kernels. Rebuilds the plans, sizes
 // the partial slots and the persistent grid, allocates or releases the
@@ -1413,30 +1487,20 @@ exc_status configure(exc_ctx* c, const FusedKCfg* f, hipStream_t st) {
   if (!need_ws && c->d_dsp) { hipFree(c->d_dsp); c->d_dsp = nullptr; }
   // only the plan of the context's path: one item per pair (or n'' chunk) for the batched
   // path, one per (n'' chunk, row block) for one launch per pair
+  free_chunk_plans(c);
+  if (c->h64) {                                   // (one workgroup per item: no persistent grid)
+    TRY(build_plans64(c, false));
+    const exc_status s = alloc_partials(c);
+    if (s != EXC_ENOMEM) return s;
+    c->err.clear();                               // (no room for the finer items' partials)
+    TRY(build_plans64(c, true));
+    return alloc_partials(c);
+  }
   free_plan(c->plain);
   free_plan(c->bat);
-  free_plan(c->perk);
-  free_chunk_plans(c);
-  if (c->h64) {
-    if (!c->batched) TRY(build_plan64(c, c->plain, 2, 0));
-    else TRY(build_plan64(c, c->bat, 0, c->n_k == 1 ? noalloc_slots(c) : 0));
-    if (c->batched && c->n_k > 1) TRY(build_plan64(c, c->perk, 1, noalloc_slots(c)));
-  } else if (c->batched) {
-    TRY(build_plan(c, c->bat, 0));
-  } else {
-    TRY(build_plan(c, c->plain, 1));
-  }
-  const size_t nslot = std::max({c->plain.n_slots, c->bat.n_slots, c->perk.n_slots});
-  const size_t asz = c->precision == EXC_FP64 ? 8 : 4;
-  hipFree(c->d_gpart);
-  hipFree(c->d_dpart);
-  c->d_gpart = nullptr;
-  c->d_dpart = nullptr;
-  TRY(dalloc(c, (char**)&c->d_gpart, nslot * c->gstride * asz));
-  TRY(dalloc(c, &c->d_dpart, nslot * (size_t)c->dstride));
-  HIPCHK(c, hipMemset(c->d_gpart, 0, nslot * c->gstride * asz));
-  HIPCHK(c, hipMemset(c->d_dpart, 0, nslot * (size_t)c->dstride * 8));
-  if (c->h64) return EXC_OK;                      // (one workgroup per item: no persistent grid)
+  if (c->batched) TRY(build_plan(c, c->bat, 0));
+  else TRY(build_plan(c, c->plain, 1));
+  TRY(alloc_partials(c));
   const void* main_fn = c->fused ? (const void*)c->fcfg->fn : (const void*)c->cfg->fn;
   const int main_threads = c->fused ? c->fcfg->nt : 64 * c->cfg->NW();
   hipFuncAttributes fa{};

@@ -62,13 +62,15 @@ void runs64(const System64& c, const Shape64& k, int groups, int nd, F&& push) {
 // one k of the ZnO-like workload takes 7.6 ms with one item per part of a pair, 6.9 ms with the items of a few
 // passes that this picks), plus the traffic of the partial slots. `launches` are the dense rows of the pairs of each launch
 // of the plan; the time is that of launch `at`, but every launch keeps to max_slots items (0: 2 GiB of partials), unless it
-// has more pairs than that (no split would do). The coarsest split (one item per pair) always qualifies.
+// has more pairs than that (no split would do), and all launches together to total_slots (0: no limit). The coarsest
+// split (one item per pair) always qualifies.
 //
 // Pairs of the same nd have the same items, and a split whose schedule cannot be shorter than the best so far (work over
 // CUs, longest item) needs none: 288 pairs of 144 different nd 11.5 -> 3.1 ms, 4096 small pairs 17 -> 0.3 ms against
 // every item listed, sorted and scheduled for every split.
 inline Split64 pick_split64(const System64& c, const std::vector<Shape64>& shapes, int nbt,
-                            const std::vector<std::vector<int>>& launches, int at, size_t max_slots) {
+                            const std::vector<std::vector<int>>& launches, int at, size_t max_slots,
+                            size_t total_slots) {
   struct Group { double cost; size_t n; };               // n items of a cost
   static const int kGroups[6] = {1, 2, 3, 4, 6, 0}, kPasses[4] = {0, 4, 2, 1};
   Split64 best;
@@ -83,7 +85,7 @@ inline Split64 pick_split64(const System64& c, const std::vector<Shape64>& shape
   sizes.erase(std::unique(sizes.begin(), sizes.end()), sizes.end());
   std::vector<size_t> parts(sizes.back() + 1);           // runs of a pair of nd dense rows under one grouping
   std::vector<Group> runs[6], items;
-  size_t most[6];                                        // most items of a launch in one run of passes
+  size_t most[6], all[6];                                // items in one run of passes: most of a launch, of the plan
   std::vector<double> h;
   for (int i = 0; i < (int)shapes.size(); ++i) {
     const Shape64& k = shapes[i];
@@ -93,12 +95,12 @@ inline Split64 pick_split64(const System64& c, const std::vector<Shape64>& shape
         parts[x] = 0;
         runs64(c, k, kGroups[g], x, [&](int, int, double) { ++parts[x]; });
       }
-      most[g] = 0;
+      most[g] = all[g] = 0;
       for (const auto& l : launches) {
-        if (l.size() > max_slots && &l != &launches[at]) continue;
         size_t n = 0;
         for (int x : l) n += parts[x];
-        most[g] = std::max(most[g], n);
+        all[g] += n;
+        if (l.size() <= max_slots || &l == &launches[at]) most[g] = std::max(most[g], n);
       }
       runs[g].clear();
       for (size_t a = 0, b; a < nd.size(); a = b) {
@@ -123,7 +125,9 @@ inline Split64 pick_split64(const System64& c, const std::vector<Shape64>& shape
           sum += x.cost * x.n;
           mx = std::max(mx, x.cost);
         }
-        if (most[g] * ((npass + per - 1) / per) > max_slots && !(passes == 0 && kGroups[g] == 1)) continue;
+        const size_t np = (npass + per - 1) / per;
+        const bool over = most[g] * np > max_slots || (total_slots && all[g] * np > total_slots);
+        if (over && !(passes == 0 && kGroups[g] == 1)) continue;
         const bool many = n > 64 * n_cu;
         const double extra = (many || n > n_cu * (k.nw == 4 ? 2 : 1) ? 0.5 * mx : 0.0) +
                              (double)n * c.slot_bytes * 2 / 5e12 * 2.4e9 / 64;

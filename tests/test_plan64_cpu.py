@@ -66,15 +66,15 @@ static Split64 plain(const System64& c, const std::vector<Shape64>& sh, int nbt,
   }
   return best;
 }
-// each line: nbt n_occ n_s n_chunk max_slots pairs nd... launches (pairs nd...)...: the split is chosen for the first ones,
+// each line: nbt n_occ n_s n_chunk max_slots total_slots pairs nd... launches (pairs nd...)...: the split is chosen for the first ones,
 // the launches after them keep to the limit too; out: the two choices and the items of each (the plain form sees the first
 // launch only), microseconds of each, items of the further launches under the plain choice and under the planner's
 int main() {
   std::vector<Shape64> sh;
   for (auto& x : (int[][2]){INSTANCES}) sh.push_back(shape(x[0], x[1]));
   int nbt, n_occ, n_s, n_chunk, pairs;
-  size_t max;
-  while (scanf("%d %d %d %d %zu %d", &nbt, &n_occ, &n_s, &n_chunk, &max, &pairs) == 6) {
+  size_t max, total;
+  while (scanf("%d %d %d %d %zu %zu %d", &nbt, &n_occ, &n_s, &n_chunk, &max, &total, &pairs) == 7) {
     std::vector<int> nd(pairs);
     for (int& x : nd) if (scanf("%d", &x) != 1) return 1;
     std::vector<std::vector<int>> all(1, nd);
@@ -90,7 +90,7 @@ int main() {
     const auto a = std::chrono::steady_clock::now();
     const Split64 p = plain(c, sh, nbt, nd, max);
     const auto b = std::chrono::steady_clock::now();
-    const Split64 q = pick_split64(c, sh, nbt, all, 0, max);
+    const Split64 q = pick_split64(c, sh, nbt, all, 0, max, total);
     const auto e = std::chrono::steady_clock::now();
     for (const Split64& s : {p, q}) {
       size_t n = 0;
@@ -127,7 +127,7 @@ def planner(tmp_path_factory):
     def run(cases):
         def line(c):
             more = c[6] if len(c) > 6 else []
-            return [*c[:5], len(c[5]), *c[5], len(more), *(x for l in more for x in [len(l), *l])]
+            return [*c[:5], c[7] if len(c) > 7 else 0, len(c[5]), *c[5], len(more), *(x for l in more for x in [len(l), *l])]
 
         text = "\n".join(" ".join(map(str, line(c))) for c in cases)
         out = subprocess.run([str(d / "plan")], input=text, capture_output=True, text=True, check=True, timeout=300)
@@ -189,3 +189,19 @@ def test_every_launch_keeps_to_the_limit(planner):
         assert q[3] <= case[4] and max(items[n:]) <= case[4], (case, q, items)
         over += max(items[:n]) > case[4]
     assert over >= 3                     # (the split of the first launch alone exceeds the limit in the others)
+
+
+def test_all_launches_keep_to_the_total(planner):
+    """One launch per pair: the split of the largest one, for all of them within a total of partial slots."""
+    rng = random.Random(11)
+    cases = []
+    for _ in range(60):
+        nd = sorted(_nd(rng, rng.randint(2, 80), 1, 900), reverse=True)
+        cases.append((rng.randint(1, 16), rng.randint(1, 20), 0, 0, 0, nd[:1], [[x] for x in nd[1:]],
+                      len(nd) + rng.randint(0, 2000)))
+    over = 0
+    for case, (p, q, _, _, items) in zip(cases, planner(cases)):
+        n = len(case[6])
+        assert q[3] + sum(items[n:]) <= case[7], (case, q)
+        over += p[3] + sum(items[:n]) > case[7]
+    assert over >= 10
