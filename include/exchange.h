@@ -328,6 +328,8 @@ void exchange_destroy(exc_ctx *ctx);
  *              likewise, 3: a work item per n'' pass and row chunk (unbatched path);
  *              17 / 18 = rows per chunk in the block-sparse / dense rows
  *   what = 19: rows of a dense row block of the fused kernel (-1 without it)
+ *   what = 20: batches of pairs that the last exchange_matrix call cut into their row
+ *              chunks, to fill the GPU with few pairs (0: one work item per pair)
  *   what = 5, 6, 7: see exchange_timing
  */
 exc_status exchange_query(const exc_ctx *ctx, int32_t what, double *value);

@@ -1,0 +1,43 @@
+"""When a call of few pairs goes through their row chunks: never where that splits nothing, otherwise in the instances that
+stream their Gram tiles; in one batch of pairs or several; with the bits of one item per pair.
+"""
+import os
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _context(nb, npw, ch, nocc, precision):
+    import paper_1003_0524_amd as lib
+    rng = np.random.default_rng(7)
+    E = []
+    for n in npw:
+        x = (rng.standard_normal((len(ch) + n,) * 2) + 1j * rng.standard_normal((len(ch) + n,) * 2)) / np.sqrt(8 * (len(ch) + n))
+        E.append(x @ x.conj().T + np.eye(len(ch) + n))
+    D = [1.5 * np.eye(b - 1, dtype=complex) for b in ch]
+    C = [0.1 * rng.standard_normal(b - 1) + 0.05j for b in ch]
+    return lib.Exchange([nb], npw, list(ch), nocc, E, D, C, precision=precision)
+
+
+def _both(ex, nb, npw, ch, nocc, dt=torch.complex128):
+    g = torch.Generator(device="cuda").manual_seed(2)
+    M = torch.randn(nocc * nb * sum(n + sum(ch) for n in npw), generator=g, dtype=dt, device="cuda")
+    V = ex.matrix(0, M).clone()
+    batches = int(ex.query(20))
+    one = ex.matrix_noalloc(0, M, torch.empty(nb * nb, dtype=torch.complex128, device="cuda"))
+    assert torch.equal(V, one)
+    return batches
+
+
+@pytest.mark.parametrize("precision", ["bf16x3", "bf16x6", "fp32"])
+@pytest.mark.parametrize("npw,nocc", [([20], 1), ([64, 63, 1], 1), ([40] * 5, 1)])
+def test_nothing_to_split(npw, nocc, precision):
+    for nb in (64, 80, 128):
+        ex = _context(nb, npw, (), nocc, precision)
+        try:
+            assert _both(ex, nb, npw, (), nocc) == 0
+        finally:
+            ex.close()
