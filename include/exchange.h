@@ -329,7 +329,8 @@ void exchange_destroy(exc_ctx *ctx);
  *              17 / 18 = rows per chunk in the block-sparse / dense rows
  *   what = 19: rows of a dense row block of the fused kernel (-1 without it)
  *   what = 20: batches of pairs that the last exchange_matrix call cut into their row
- *              chunks, to fill the GPU with few pairs (0: one work item per pair)
+ *              chunks, to fill the GPU with few pairs (0: one work item per pair);
+ *              what = 21: how often there was no memory for that
  *   what = 5, 6, 7: see exchange_timing
  */
 exc_status exchange_query(const exc_ctx *ctx, int32_t what, double *value);
@@ -351,7 +352,8 @@ exc_status exchange_query(const exc_ctx *ctx, int32_t what, double *value);
  * kernel of their own); EXC_SPARSE_NCW=1|2|4 fixes the
  * columns each wavefront of the block-sparse kernel takes (HERK form);
  * EXC_HERK64=<id>,<passes>,<groups> fixes the FP64 kernel's instance (what = 3), n'' passes
- * per item (0: all) and runs of row parts per pair (0: a part each); EXC_GRAPH=1
+ * per item (0: all) and runs of row parts per pair (0: a part each);
+ * EXC_CHUNK_BYTES=<n> the memory of a batch of row chunks (what = 20; 256 MiB); EXC_GRAPH=1
  * replays the batched launch from a HIP graph instead of enqueueing its kernels.
  */
 

@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <numeric>
 #include <string>
 #include <map>
@@ -221,6 +222,9 @@ struct exc_ctx {
   float* d_gchunk = nullptr;
   double* d_dchunk = nullptr;
   size_t chunk_cap = 0;               // slots
+  size_t chunk_fail = SIZE_MAX;       // fewest slots that there was no room for
+  int chunk_fails = 0;                // allocations that failed
+  size_t chunk_bytes = (size_t)256 << 20;  // of the slots of a batch (EXC_CHUNK_BYTES)
   int chunk_batches = 0;              // batches of the last exchange_matrix call (0: one item per pair)
   hipEvent_t ev_chunk = nullptr;      // the last use of the chunk slots
   bool tab_pending = false;
@@ -361,6 +365,7 @@ void free_chunk_plans(exc_ctx* c) {
   c->d_gchunk = nullptr;
   c->d_dchunk = nullptr;
   c->chunk_cap = 0;
+  c->chunk_fail = SIZE_MAX;
 }
 
 void release_timing(exc_ctx* c) {
@@ -1091,8 +1096,7 @@ void launch_k(exc_ctx* c, const Plan& P, int dtype, int k, hipStream_t st) {
 // other roundings. Items per n'' chunk and row part that keep every chunk of 64 rows in a slot of its own, added up in
 // the chain's order afterwards, give the same bits from a full GPU: the first V(k) of the ZnO-like workload (144 pairs
 // of 18 n'', bf16x3) 13.4 -> 4.1 ms. The slots are written and read once (12 MB a pair there); batches of pairs keep
-// them within kChunkBytes, about the size of the memory-side cache. A plan without batches: not for this k.
-constexpr size_t kChunkBytes = (size_t)256 << 20;
+// them within chunk_bytes, about the size of the memory-side cache. A plan without batches: not for this k.
 exc_status chunk_plan(exc_ctx* c, int k, ChunkPlan** out) {
   *out = nullptr;
   const FusedKCfg* f = c->fcfg;
@@ -1128,8 +1132,8 @@ exc_status chunk_plan(exc_ctx* c, int k, ChunkPlan** out) {
       P.npass = (c->n_occ + ngmax - 1) / ngmax;
       const int ngc = (c->n_occ + P.npass - 1) / P.npass, cpp = n_sc + (p.nd + 63) / 64;
       const size_t need = (size_t)P.npass * cpp;
-      if (need * slot_b > kChunkBytes) { P = ChunkPlan{}; items.clear(); break; }
-      if ((slots + need) * slot_b > kChunkBytes) flush(i);
+      if (need * slot_b > c->chunk_bytes) { P = ChunkPlan{}; items.clear(); break; }
+      if ((slots + need) * slot_b > c->chunk_bytes) flush(i);
       base.push_back((int32_t)slots);
       const int nparts = fused_parts(c, p);
       for (int g = 0; g < P.npass; ++g) {
@@ -1147,23 +1151,40 @@ exc_status chunk_plan(exc_ctx* c, int k, ChunkPlan** out) {
     // (nothing to split: the merge would only come on top, one pair of 20 rows and 64 bands in bf16x3 22.7 -> 24.6 us)
     if (items.size() == (size_t)(p1 - p0)) P = ChunkPlan{};
     if (!P.batches.empty()) {
-      TRY(upload(c, &P.d_items, items));
-      const exc_status s = upload(c, &P.d_base, base);
-      if (s != EXC_OK) { hipFree(P.d_items); return s; }
+      exc_status s = upload(c, &P.d_items, items);
+      if (s == EXC_OK) s = upload(c, &P.d_base, base);
+      if (s != EXC_OK) {
+        hipFree(P.d_items);
+        hipFree(P.d_base);
+        if (s != EXC_ENOMEM) return s;
+        ++c->chunk_fails;
+        c->err.clear();
+        P = ChunkPlan{};
+      }
     }
     found = c->chunk_plans.emplace(k, P).first;
   }
   ChunkPlan& P = found->second;
   if (P.batches.empty()) return EXC_OK;
+  if (P.slots >= c->chunk_fail) return EXC_OK;         // (there was no room: not asked for again)
   if (P.slots > c->chunk_cap) {
-    HIPCHK(c, hipDeviceSynchronize());
+    float* g = nullptr;
+    double* d = nullptr;
+    exc_status s = dalloc(c, &g, P.slots * c->gstride);
+    if (s == EXC_OK) s = dalloc(c, &d, P.slots * (size_t)64 * f->NCT);
+    if (s != EXC_OK) {
+      hipFree(g);
+      if (s != EXC_ENOMEM) return s;
+      ++c->chunk_fails;
+      c->chunk_fail = P.slots;
+      c->err.clear();
+      return EXC_OK;
+    }
+    if (c->chunk_cap) HIPCHK(c, hipDeviceSynchronize());   // earlier calls still use the smaller ones
     hipFree(c->d_gchunk);
     hipFree(c->d_dchunk);
-    c->d_gchunk = nullptr;
-    c->d_dchunk = nullptr;
-    c->chunk_cap = 0;
-    TRY(dalloc(c, &c->d_gchunk, P.slots * c->gstride));
-    TRY(dalloc(c, &c->d_dchunk, P.slots * (size_t)64 * f->NCT));
+    c->d_gchunk = g;
+    c->d_dchunk = d;
     c->chunk_cap = P.slots;
   }
   if (!c->ev_chunk) HIPCHK(c, hipEventCreateWithFlags(&c->ev_chunk, hipEventDisableTiming));
@@ -1230,9 +1251,11 @@ exc_status run_k_batched(exc_ctx* c, int k, int dtype, hipStream_t st) {
   // (no room for the chunks: one item per pair; a captured call keeps to that too, as its replays may run beside
   // other calls of the context)
   if (c->fused && !capturing(st)) {
-    const exc_status s = chunk_plan(c, k, &cp);
-    if (s == EXC_ENOMEM) c->err.clear();
-    else if (s != EXC_OK) return s;
+    try {
+      TRY(chunk_plan(c, k, &cp));
+    } catch (const std::bad_alloc&) {              // (host memory for the plan: no exception leaves the library)
+      cp = nullptr;
+    }
   }
   if (cp) c->chunk_batches = (int)cp->batches.size();
   if (cp) TRY(launch_chunks(c, *cp, P, dtype, k, st));
@@ -2122,6 +2145,7 @@ exc_status exchange_init(const exc_desc* d, const exc_coulomb* cv, void* stream,
   if (const char* ev = getenv("EXC_GRAPH")) c->direct = ev[0] != '1';
   if (sparse_lds_bytes(c) > 65536)
     IHIP(hipFuncSetAttribute(sparse_fn(c), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sparse_lds_bytes(c)));
+  if (const char* ev = getenv("EXC_CHUNK_BYTES")) c->chunk_bytes = strtoull(ev, nullptr, 10);
   if (const char* ev = getenv("EXC_FUSED_SPLIT")) c->fsplit = std::min(2, std::max(0, atoi(ev)));   // (fixed-configuration runs)
   if (c->plain_gemm) {
     // W of the largest pair (laid out as M), the split partials of A^H W, the V(k) accumulator
@@ -2566,6 +2590,7 @@ exc_status exchange_query(const exc_ctx* c, int32_t what, double* value) {
     case 12: *value = c->gamma_terms; return EXC_OK;
     case 14: *value = c->fused && !c->batched ? std::max(c->fsplit, 1) : c->fsplit; return EXC_OK;
     case 20: *value = c->chunk_batches; return EXC_OK;
+    case 21: *value = c->chunk_fails; return EXC_OK;
     case 19: *value = c->fused ? fused_bm(*c->fcfg) : -1; return EXC_OK;
     case 15:
     case 16:

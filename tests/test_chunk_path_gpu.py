@@ -41,3 +41,23 @@ def test_nothing_to_split(npw, nocc, precision):
             assert _both(ex, nb, npw, (), nocc) == 0
         finally:
             ex.close()
+
+
+def test_no_room_is_remembered():
+    """230 pairs of 10 300 passes, a slot each: 350 GB, more than the card has. The call falls back to one item per pair,
+    and the next one does not ask again."""
+    nb, nocc, npw = 128, 10300, [1] * 230
+    os.environ["EXC_CHUNK_BYTES"] = str(1 << 50)
+    try:
+        ex = _context(nb, npw, (), nocc, "bf16x3")
+    finally:
+        del os.environ["EXC_CHUNK_BYTES"]
+    try:
+        slot = 136 * 256 * 4 + 64 * 16 * 8
+        assert len(npw) * nocc * slot > torch.cuda.mem_get_info()[1]
+        assert _both(ex, nb, npw, (), nocc, torch.complex64) == 0
+        assert ex.query(21) == 1
+        assert _both(ex, nb, npw, (), nocc, torch.complex64) == 0
+        assert ex.query(21) == 1
+    finally:
+        ex.close()
