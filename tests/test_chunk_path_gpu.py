@@ -61,3 +61,31 @@ def test_no_room_is_remembered():
         assert ex.query(21) == 1
     finally:
         ex.close()
+
+
+# (bands, plane waves, channels, n_occ, bytes that hold the largest pair's slots but not all pairs'): instances of 13 and
+# 16 band tiles
+CASES = {"80 bands": (80, [130, 64, 191, 40], [4] * 12, 4, 2 << 20), "100 bands": (100, [200] * 6, [3] * 9, 3, 4 << 20),
+         "128 bands": (128, [60, 129], [2] * 40, 5, 5 << 20)}
+
+
+@pytest.mark.parametrize("dt", ["c128", "c64"])
+@pytest.mark.parametrize("precision", ["bf16x3", "bf16x6", "fp32"])
+@pytest.mark.parametrize("name", list(CASES))
+def test_one_batch_and_several(name, precision, dt):
+    nb, npw, ch, nocc, few = CASES[name]
+    tdt = torch.complex128 if dt == "c128" else torch.complex64
+    seen = {}
+    for limit in (None, few):
+        if limit:
+            os.environ["EXC_CHUNK_BYTES"] = str(limit)
+        try:
+            ex = _context(nb, npw, ch, nocc, precision)
+        finally:
+            os.environ.pop("EXC_CHUNK_BYTES", None)
+        try:
+            assert ex.query(16) == 1                     # an instance that streams its Gram tiles
+            seen[limit] = _both(ex, nb, npw, ch, nocc, tdt)
+        finally:
+            ex.close()
+    assert seen[None] == 1 and seen[few] >= 2, seen
