@@ -302,12 +302,14 @@ void exchange_destroy(exc_ctx *ctx);
  *   what = 1: nominal flops of the method per exchange_matrix_all (sparse-aware,
  *             complex multiply-add = 8 flops, Hermitian upper triangle only)
  *   what = 2: flops the chosen form executes per exchange_matrix_all (padding included)
- *   what = 3: id of the main kernel's configuration (a fused instance, or the
- *             tile kernel of the block-sparse + tile path)
+ *   what = 3: id of the main kernel's configuration (a fused instance, the
+ *             tile kernel of the block-sparse + tile path, or the FP64 Cholesky/HERK
+ *             kernel: 2000 + 16 x band tiles + n'' values per pass)
  *   what = 8: how it was chosen: 0 default, 1 timed by the autotuner on the first
  *             batched exchange_matrix_all, 2 read from the EXC_TUNE_CACHE file
  *   what = 9: bytes of the block-sparse workspace of the block-sparse + tile path
- *             (written once and read once per exchange_matrix_all on that path)
+ *             (written once and read once per exchange_matrix_all on that path; not
+ *             allocated where the main kernel forms the block-sparse rows itself)
  *   what = 10: 1 if the fused kernel serves the batched path, else 0
  *   what = 4: algorithmic HBM bytes of one exchange_matrix_all
  *             (M read once, v(q) read once, Vx written once)
@@ -364,7 +366,8 @@ exc_status exchange_query(const exc_ctx *ctx, int32_t what, double *value);
  * EXC_GRAPH=1), and each call records into its own slot of a pool of n_slots
  * event triples (the last n_slots calls are kept). n_slots = 0 switches timing
  * off. Both synchronise the device and drop the current graph. Read the means with
- * exchange_query: what = 5 tile kernel ms, 7 sparse kernel ms, 6 replays timed.
+ * exchange_query: what = 5 main kernel ms, 7 sparse kernel ms (0 where the main kernel
+ * forms the block-sparse rows itself), 6 replays timed.
  */
 exc_status exchange_timing(exc_ctx *ctx, int32_t n_slots);
 

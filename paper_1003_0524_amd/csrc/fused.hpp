@@ -128,7 +128,9 @@ struct FusedCfg {
   // binary32 Gram chains (for error models): one per item, or (GSTREAM) one per GR-row
   // chunk added into the item's partial; GR rows per chunk in both row kinds
   static constexpr int GCHAIN = GSTREAM ? 1 : 0, GCH_RS = GR, GCH_RD = GR;
-  // the block-sparse rows on the FP64 matrix cores (rows.hpp): a small ragged FP32 system (8 column tiles) 105 -> 90 us.
+  // the block-sparse rows on the FP64 matrix cores (rows.hpp), FP32 above 6 column tiles: a small ragged system (8 tiles)
+  // 105 -> 90 us; complex64 M 4-15 % (24 bands, 512 pairs, 12 tiles 583 -> 493 us; 60 bands, 24 q, 8 tiles 7.45 -> 7.08
+  // ms; 100 bands, 12 q, 13 tiles 16.6 -> 15.9; 120 bands, 16 tiles 15.5 -> 14.6), complex128 M 0-4 % in the same.
   // Elsewhere the vector cores stay ahead: Si-like bf16x3 256 us against 272, FP32 (6 column tiles) 477 against 506.
   // (Real-factor instances would gain, 126 -> 114 us, but give the bits of their general twins.)
   static constexpr bool MFMA_ROWS = MODE == M_F32 && NCT > 6;
