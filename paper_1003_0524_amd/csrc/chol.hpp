@@ -5,8 +5,8 @@
 // Bound by the FP64 matrix cores in the middle of the factorisation, by the diagonal tile's serial chain (about
 // 28 us a column) and by few tiles at its end. All tiles of all q of a column are one launch: one workgroup per q
 // for the whole factorisation, its products on the vector cores, left 112 of the 256 CUs idle with 144 q and waited
-// for the largest: 144 matrices of order 372-944 (ZnO-like) 18.9 -> 3.3 ms, 64 of order 310
-// (Si-like) 2.4 -> 0.39 ms.
+// for the largest: 144 matrices of order 372-944 (ZnO-like) 18.9 -> 3.5 ms, 64 of order 310
+// (Si-like) 2.4 -> 0.43 ms.
 // Left-looking: a tile is read and written once, where a right-looking update would rewrite the whole trailing
 // matrix (1 GB here, four times the memory-side cache) per column.
 #pragma once
