@@ -38,7 +38,11 @@
  * return without waiting when on_device = 1; inputs must stay valid and
  * outputs must not be read until the stream has reached that point. With
  * on_device = 0 the call copies from / to host memory and returns when the
- * result is on the host.
+ * result is on the host. Calls of one context for different k may be enqueued on
+ * different streams (from one host thread at a time): where they share buffers the
+ * library makes one wait for the other. Calls for the same k are the caller's to order,
+ * and so are replays of captured calls beside others where the main kernel does not form
+ * the block-sparse rows itself.
  *
  * Around the exchange matrix: exchange_energy[_device] (eq. "HF exchange
  * energy"); exchange_gamma_term (the q -> 0 term, Sec. III.E); the symmetry

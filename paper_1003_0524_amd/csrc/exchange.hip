@@ -236,6 +236,9 @@ struct exc_ctx {
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   hipEvent_t ev_en = nullptr;         // end of the last energy call (its buffers are shared)
   bool ev_en_set = false;
+  hipEvent_t ev_shared = nullptr;     // last use of the workspace or the unbatched GEMM form's buffers
+  hipStream_t shared_st = nullptr;    //  and its stream, if there was one
+  bool shared_used = false;
   hipEvent_t ev_learn = nullptr;      // end of the last learned call (its buffers are shared)
   bool learn_set = false;             // (it was asynchronous)
   int g_dtype = -1;
@@ -335,6 +338,38 @@ exc_status ensure_ws(exc_ctx* c, size_t bytes) {
   return EXC_OK;
 }
 
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
+
+// Buffers that one call at a time may use: the block-sparse workspace (a per-k call keeps its rows at its start, whatever
+// the k) and those of the unbatched GEMM form. A call on another stream than the last one comes after it; a context that
+// stays on one stream records no event (3 us a call). A captured call cannot wait for an event from outside: its replays
+// must not run beside other calls of the context.
+exc_status shared_begin(exc_ctx* c, hipStream_t st) {
+  if (capturing(st)) return EXC_OK;
+  if (c->shared_used && !c->ev_shared && st != c->shared_st && !capturing(c->shared_st)) {
+    HIPCHK(c, hipEventCreateWithFlags(&c->ev_shared, hipEventDisableTiming));
+    if (hipEventRecord(c->ev_shared, c->shared_st) != hipSuccess) {   // (that stream is gone)
+      (void)hipGetLastError();
+      HIPCHK(c, hipDeviceSynchronize());
+    }
+  }
+  if (c->ev_shared) HIPCHK(c, hipStreamWaitEvent(st, c->ev_shared, 0));
+  return EXC_OK;
+}
+
+exc_status shared_end(exc_ctx* c, hipStream_t st) {
+  if (capturing(st)) return EXC_OK;
+  c->shared_used = true;
+  c->shared_st = st;
+  if (c->ev_shared) HIPCHK(c, hipEventRecord(c->ev_shared, st));
+  return EXC_OK;
+}
+
 // Workspace base for the pairs of k (k < 0: every pair). Pair offsets are global; a
 // per-k call keeps only its own pairs' rows, so the base is shifted back by the
 // first offset of k (an address the kernels never form below the allocation).
@@ -390,7 +425,8 @@ void release(exc_ctx* c) {
   free_chunk_plans(c);
   if (c->ev_en) hipEventDestroy(c->ev_en);
   if (c->ev_learn) hipEventDestroy(c->ev_learn);
-  c->ev_en = c->ev_learn = nullptr;
+  if (c->ev_shared) hipEventDestroy(c->ev_shared);
+  c->ev_en = c->ev_learn = c->ev_shared = nullptr;
   if (c->ev_out) hipEventDestroy(c->ev_out);
   if (c->own) hipStreamDestroy(c->own);
   for (hipEvent_t& e : c->ev_g) if (e) hipEventDestroy(e);
@@ -761,13 +797,6 @@ const KernelCfg* pick_cfg(int mode, int form, int nbt_max) {
   return best;
 }
 
-bool capturing(hipStream_t st) {
-  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &s) == hipSuccess) return s != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();
-  return false;
-}
-
 // Writes n pointers to one or two device tables, in the order of st.
 exc_status put_pointers(exc_ctx* c, int n, void** dst0, const void* const* src0, void** dst1, const void* const* src1,
                         hipStream_t st) {
@@ -949,6 +978,13 @@ const void* sparse_fn(const exc_ctx* c) {
 bool fused64(const exc_ctx* c) { return c->h64 && c->n_chunk64 > 0; }
 // The call needs the block-sparse workspace.
 bool needs_ws(const exc_ctx* c) { return !c->fused && !fused64(c); }
+
+// The call uses buffers that only one call at a time may (shared_begin).
+bool shares(const exc_ctx* c) {
+  if (c->plain_gemm) return true;
+  const bool packs = c->form == EXC_FORM_CHOL_HERK && c->precision != EXC_FP64;   // (as in cfg_sparse)
+  return needs_ws(c) && (packs || c->n_s > 0 || (c->form != EXC_FORM_CHOL_HERK && c->n_ch > 0));
+}
 
 // Block-sparse rows of pairs [pair0, pair0 + npairs), all of k (k < 0: every pair). Returns
 // false when there is nothing to do.
@@ -2211,10 +2247,13 @@ exc_status exchange_matrix(exc_ctx* c, int32_t k, const void* M, int32_t dtype, 
   void* vp[1] = {Vd};
   TRY(fit_dtype(c, dtype, st));
   TRY(set_tables(c, k, 1, mp, vp, st));
+  const bool shared = shares(c);
+  if (shared) TRY(shared_begin(c, st));
   if (c->plain_gemm) TRY(run_k_plain_gemm(c, k, dtype, st));
   else if (c->batched) TRY(run_k_batched(c, k, dtype, st));
   else TRY(run_k_plain(c, k, dtype, st));
   HIPCHK(c, hipGetLastError());
+  if (shared) TRY(shared_end(c, st));
   if (!on_device) {
     HIPCHK(c, hipMemcpyAsync(Vx, c->d_vres + c->v_off[k], (size_t)c->nb[k] * c->nb[k] * 16,
                              hipMemcpyDeviceToHost, st));
@@ -2291,9 +2330,12 @@ exc_status exchange_matrix_all(exc_ctx* c, const void* const* M_k, int32_t dtype
   if (!c->batched) {
     TRY(fit_dtype(c, dtype, st));
     TRY(set_tables(c, 0, c->n_k, M_k, Vx_k, st));
+    const bool shared = shares(c);
+    if (shared) TRY(shared_begin(c, st));
     for (int k = 0; k < c->n_k; ++k)
       TRY(c->plain_gemm ? run_k_plain_gemm(c, k, dtype, st) : run_k_plain(c, k, dtype, st));
     HIPCHK(c, hipGetLastError());
+    if (shared) TRY(shared_end(c, st));
   } else {
     if (!c->tune_done) {
       const char* ev = getenv("EXC_TUNE");
@@ -2310,9 +2352,12 @@ exc_status exchange_matrix_all(exc_ctx* c, const void* const* M_k, int32_t dtype
       c->tune_done = true;
     }
     TRY(fit_dtype(c, dtype, st));                  // (a fixed or earlier choice may read complex64 only)
+    const bool shared = shares(c);
+    if (shared) TRY(shared_begin(c, st));
     if (c->direct) {
       TRY(set_tables(c, 0, c->n_k, M_k, Vx_k, st));
       TRY(launch_batched_direct(c, dtype, st));
+      if (shared) TRY(shared_end(c, st));
       for (int k = 0; k < c->n_k; ++k) c->v_valid[k] = 1;
       return EXC_OK;
     }
@@ -2333,6 +2378,7 @@ exc_status exchange_matrix_all(exc_ctx* c, const void* const* M_k, int32_t dtype
       c->t_count = std::min(c->t_count + 1, c->t_slots);
     }
     HIPCHK(c, hipGraphLaunch(c->gexec, st));     // in order with the caller's work on st
+    if (shared) TRY(shared_end(c, st));
   }
   for (int k = 0; k < c->n_k; ++k) c->v_valid[k] = 1;
   return EXC_OK;
