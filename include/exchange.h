@@ -42,7 +42,8 @@
  * different streams (from one host thread at a time): where they share buffers the
  * library makes one wait for the other. Calls for the same k are the caller's to order,
  * and so are replays of captured calls beside others where the main kernel does not form
- * the block-sparse rows itself.
+ * the block-sparse rows itself. The energy, the Gamma-point term and the back-transform
+ * follow the last exchange_matrix[_all] call, not earlier ones on other streams.
  *
  * Around the exchange matrix: exchange_energy[_device] (eq. "HF exchange
  * energy"); exchange_gamma_term (the q -> 0 term, Sec. III.E); the symmetry

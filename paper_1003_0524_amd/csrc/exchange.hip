@@ -125,6 +125,13 @@ struct ChunkPlan {
   size_t slots = 0;                 // of the largest batch
 };
 
+// The last use of buffers that one call at a time may use (turn_begin).
+struct Turn {
+  hipEvent_t ev = nullptr;            // its end (created once a second stream uses them)
+  hipStream_t st = nullptr;
+  bool used = false;
+};
+
 }  // namespace
 
 struct NnState;        // learned extrapolator (nn_abi.hpp)
@@ -236,9 +243,7 @@ struct exc_ctx {
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
   hipEvent_t ev_en = nullptr;         // end of the last energy call (its buffers are shared)
   bool ev_en_set = false;
-  hipEvent_t ev_shared = nullptr;     // last use of the workspace or the unbatched GEMM form's buffers
-  hipStream_t shared_st = nullptr;    //  and its stream, if there was one
-  bool shared_used = false;
+  Turn turn_ws, turn_bt;              // the workspace or the unbatched GEMM form's buffers; the back-transform's
   hipEvent_t ev_learn = nullptr;      // end of the last learned call (its buffers are shared)
   bool learn_set = false;             // (it was asynchronous)
   int g_dtype = -1;
@@ -346,27 +351,27 @@ bool capturing(hipStream_t st) {
 }
 
 // Buffers that one call at a time may use: the block-sparse workspace (a per-k call keeps its rows at its start, whatever
-// the k) and those of the unbatched GEMM form. A call on another stream than the last one comes after it; a context that
-// stays on one stream records no event (3 us a call). A captured call cannot wait for an event from outside: its replays
-// must not run beside other calls of the context.
-exc_status shared_begin(exc_ctx* c, hipStream_t st) {
+// the k), those of the unbatched GEMM form, the back-transform's T. A call on another stream than the last one comes after
+// it; a context that stays on one stream records no event (3 us a call). A captured call cannot wait for an event from
+// outside: its replays must not run beside other calls of the context.
+exc_status turn_begin(exc_ctx* c, Turn& t, hipStream_t st) {
   if (capturing(st)) return EXC_OK;
-  if (c->shared_used && !c->ev_shared && st != c->shared_st && !capturing(c->shared_st)) {
-    HIPCHK(c, hipEventCreateWithFlags(&c->ev_shared, hipEventDisableTiming));
-    if (hipEventRecord(c->ev_shared, c->shared_st) != hipSuccess) {   // (that stream is gone)
+  if (t.used && !t.ev && st != t.st && !capturing(t.st)) {
+    HIPCHK(c, hipEventCreateWithFlags(&t.ev, hipEventDisableTiming));
+    if (hipEventRecord(t.ev, t.st) != hipSuccess) {    // (that stream is gone)
       (void)hipGetLastError();
       HIPCHK(c, hipDeviceSynchronize());
     }
   }
-  if (c->ev_shared) HIPCHK(c, hipStreamWaitEvent(st, c->ev_shared, 0));
+  if (t.ev) HIPCHK(c, hipStreamWaitEvent(st, t.ev, 0));
   return EXC_OK;
 }
 
-exc_status shared_end(exc_ctx* c, hipStream_t st) {
+exc_status turn_end(exc_ctx* c, Turn& t, hipStream_t st) {
   if (capturing(st)) return EXC_OK;
-  c->shared_used = true;
-  c->shared_st = st;
-  if (c->ev_shared) HIPCHK(c, hipEventRecord(c->ev_shared, st));
+  t.used = true;
+  t.st = st;
+  if (t.ev) HIPCHK(c, hipEventRecord(t.ev, st));
   return EXC_OK;
 }
 
@@ -425,8 +430,8 @@ void release(exc_ctx* c) {
   free_chunk_plans(c);
   if (c->ev_en) hipEventDestroy(c->ev_en);
   if (c->ev_learn) hipEventDestroy(c->ev_learn);
-  if (c->ev_shared) hipEventDestroy(c->ev_shared);
-  c->ev_en = c->ev_learn = c->ev_shared = nullptr;
+  for (Turn* t : {&c->turn_ws, &c->turn_bt}) if (t->ev) hipEventDestroy(t->ev);
+  c->ev_en = c->ev_learn = c->turn_ws.ev = c->turn_bt.ev = nullptr;
   if (c->ev_out) hipEventDestroy(c->ev_out);
   if (c->own) hipStreamDestroy(c->own);
   for (hipEvent_t& e : c->ev_g) if (e) hipEventDestroy(e);
@@ -979,7 +984,7 @@ bool fused64(const exc_ctx* c) { return c->h64 && c->n_chunk64 > 0; }
 // The call needs the block-sparse workspace.
 bool needs_ws(const exc_ctx* c) { return !c->fused && !fused64(c); }
 
-// The call uses buffers that only one call at a time may (shared_begin).
+// The call uses turn_ws's buffers.
 bool shares(const exc_ctx* c) {
   if (c->plain_gemm) return true;
   const bool packs = c->form == EXC_FORM_CHOL_HERK && c->precision != EXC_FP64;   // (as in cfg_sparse)
@@ -2248,12 +2253,12 @@ exc_status exchange_matrix(exc_ctx* c, int32_t k, const void* M, int32_t dtype, 
   TRY(fit_dtype(c, dtype, st));
   TRY(set_tables(c, k, 1, mp, vp, st));
   const bool shared = shares(c);
-  if (shared) TRY(shared_begin(c, st));
+  if (shared) TRY(turn_begin(c, c->turn_ws, st));
   if (c->plain_gemm) TRY(run_k_plain_gemm(c, k, dtype, st));
   else if (c->batched) TRY(run_k_batched(c, k, dtype, st));
   else TRY(run_k_plain(c, k, dtype, st));
   HIPCHK(c, hipGetLastError());
-  if (shared) TRY(shared_end(c, st));
+  if (shared) TRY(turn_end(c, c->turn_ws, st));
   if (!on_device) {
     HIPCHK(c, hipMemcpyAsync(Vx, c->d_vres + c->v_off[k], (size_t)c->nb[k] * c->nb[k] * 16,
                              hipMemcpyDeviceToHost, st));
@@ -2331,11 +2336,11 @@ exc_status exchange_matrix_all(exc_ctx* c, const void* const* M_k, int32_t dtype
     TRY(fit_dtype(c, dtype, st));
     TRY(set_tables(c, 0, c->n_k, M_k, Vx_k, st));
     const bool shared = shares(c);
-    if (shared) TRY(shared_begin(c, st));
+    if (shared) TRY(turn_begin(c, c->turn_ws, st));
     for (int k = 0; k < c->n_k; ++k)
       TRY(c->plain_gemm ? run_k_plain_gemm(c, k, dtype, st) : run_k_plain(c, k, dtype, st));
     HIPCHK(c, hipGetLastError());
-    if (shared) TRY(shared_end(c, st));
+    if (shared) TRY(turn_end(c, c->turn_ws, st));
   } else {
     if (!c->tune_done) {
       const char* ev = getenv("EXC_TUNE");
@@ -2353,11 +2358,11 @@ exc_status exchange_matrix_all(exc_ctx* c, const void* const* M_k, int32_t dtype
     }
     TRY(fit_dtype(c, dtype, st));                  // (a fixed or earlier choice may read complex64 only)
     const bool shared = shares(c);
-    if (shared) TRY(shared_begin(c, st));
+    if (shared) TRY(turn_begin(c, c->turn_ws, st));
     if (c->direct) {
       TRY(set_tables(c, 0, c->n_k, M_k, Vx_k, st));
       TRY(launch_batched_direct(c, dtype, st));
-      if (shared) TRY(shared_end(c, st));
+      if (shared) TRY(turn_end(c, c->turn_ws, st));
       for (int k = 0; k < c->n_k; ++k) c->v_valid[k] = 1;
       return EXC_OK;
     }
@@ -2378,7 +2383,7 @@ exc_status exchange_matrix_all(exc_ctx* c, const void* const* M_k, int32_t dtype
       c->t_count = std::min(c->t_count + 1, c->t_slots);
     }
     HIPCHK(c, hipGraphLaunch(c->gexec, st));     // in order with the caller's work on st
-    if (shared) TRY(shared_end(c, st));
+    if (shared) TRY(turn_end(c, c->turn_ws, st));
   }
   for (int k = 0; k < c->n_k; ++k) c->v_valid[k] = 1;
   return EXC_OK;
@@ -2546,6 +2551,7 @@ exc_status exchange_back_transform(exc_ctx* c, int32_t k, const void* Z, int32_t
     HIPCHK(c, hipEventRecord(c->ev_out, c->last_stream));
     HIPCHK(c, hipStreamWaitEvent(st, c->ev_out, 0));
   }
+  TRY(turn_begin(c, c->turn_bt, st));
   const double2* V = c->d_vres + c->v_off[k];
   hipLaunchKernelGGL(bt_left_kernel, dim3((unsigned)((n_G + 15) / 16), (unsigned)((nb + 15) / 16)), dim3(256), 0, st,
                      (const double2*)Z, V, n_G, nb, c->d_bt);
@@ -2557,7 +2563,7 @@ exc_status exchange_back_transform(exc_ctx* c, int32_t k, const void* Z, int32_t
   HIPCHK(c, hipEventRecord(c->ev_bt[1], st));
   HIPCHK(c, hipGetLastError());
   c->bt_timed = true;
-  return EXC_OK;
+  return turn_end(c, c->turn_bt, st);
 }
 
 exc_status exchange_band_mask(exc_ctx* c, int32_t k, const uint8_t* keep) {

@@ -1,6 +1,6 @@
 """Calls of different k of one context on several streams where they share buffers: the block-sparse workspace (FP64 with a
 channel longer than the kernel's chunks, the GEMM form, the unfused reduced-precision path) and the buffers of the unbatched
-GEMM form. Against the same calls with a synchronisation after each: the same bits.
+GEMM form; and back-transforms, which share T = Z V. Against the same calls with a synchronisation after each: the same bits.
 """
 import os
 
@@ -50,5 +50,35 @@ def test_streams_in_turn(name, precision, form, batched):
         torch.cuda.synchronize()
         for k, v in got:
             assert torch.equal(v, ref[k]), (name, k)
+    finally:
+        ex.close()
+
+
+def test_back_transforms_in_turn():
+    import paper_1003_0524_amd as lib
+    rng = np.random.default_rng(8)
+    nb, n_G = [100, 60, 100], 1500
+    x = rng.standard_normal((40, 40)) + 1j * rng.standard_normal((40, 40))
+    ex = lib.Exchange(nb, [40], [], 2, [x @ x.conj().T + np.eye(40)], [], [], precision="fp64")
+    try:
+        g = torch.Generator(device="cuda").manual_seed(5)
+        Zs = []
+        for k, b in enumerate(nb):
+            ex.matrix(k, torch.randn(2 * b * 40, generator=g, dtype=torch.complex128, device="cuda"))
+            Zs.append(torch.randn((b, n_G), generator=g, dtype=torch.complex128, device="cuda").T)
+        torch.cuda.synchronize()
+        ref = []
+        for k in range(3):
+            ref.append(ex.back_transform(k, Zs[k]).clone())
+            torch.cuda.synchronize()
+        streams = [torch.cuda.Stream() for _ in range(3)]
+        got = []
+        for i in range(6):
+            for k in range(3):
+                with torch.cuda.stream(streams[(k + i) % 3]):
+                    got.append((k, ex.back_transform(k, Zs[k])))
+        torch.cuda.synchronize()
+        for k, v in got:
+            assert torch.equal(v, ref[k]), k
     finally:
         ex.close()
