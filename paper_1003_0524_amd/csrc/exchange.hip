@@ -408,6 +408,49 @@ void free_chunk_plans(exc_ctx* c) {
   c->chunk_fail = SIZE_MAX;
 }
 
+// The contexts' own streams, kept for the next context of the device instead of destroyed: after graph launches (the
+// autotuner's, a training run's) the runtime counts their completions off in the stream object for milliseconds after the
+// stream, and the device, are idle, and a destroyed stream's memory is then somebody else's. (A counter eight bytes wide,
+// stepping down by some tens, in blocks allocated after a context's end; none where the stream lived on or took plain
+// launches only.) Never more streams than contexts were alive at once; not freed at exit, where contexts may still end.
+struct OwnStreams {
+  std::mutex mu;
+  std::vector<std::pair<int, hipStream_t>> idle;   // (device, stream)
+};
+OwnStreams& own_streams() {
+  static OwnStreams* s = new OwnStreams;
+  return *s;
+}
+
+hipError_t take_own(exc_ctx* c) {
+  OwnStreams& s = own_streams();
+  {
+    std::lock_guard<std::mutex> lock(s.mu);
+    for (size_t i = s.idle.size(); i-- > 0;) {
+      if (s.idle[i].first != c->device) continue;
+      hipStream_t st = s.idle[i].second;
+      s.idle.erase(s.idle.begin() + i);
+      const hipError_t e = hipStreamQuery(st);
+      if (e == hipSuccess || e == hipErrorNotReady) {
+        c->own = st;
+        return hipSuccess;
+      }
+      (void)hipGetLastError();                     // (the device was reset: its streams are gone)
+    }
+  }
+  return hipStreamCreateWithFlags(&c->own, hipStreamNonBlocking);
+}
+
+void give_own(exc_ctx* c) {
+  if (!c->own) return;
+  OwnStreams& s = own_streams();
+  std::lock_guard<std::mutex> lock(s.mu);
+  try {
+    s.idle.push_back({c->device, c->own});
+  } catch (const std::bad_alloc&) {}               // (no room to note it: left as it is)
+  c->own = nullptr;
+}
+
 void release_timing(exc_ctx* c) {
   for (hipEvent_t e : c->tpool) hipEventDestroy(e);
   c->tpool.clear();
@@ -433,13 +476,12 @@ void release(exc_ctx* c) {
   for (Turn* t : {&c->turn_ws, &c->turn_bt}) if (t->ev) hipEventDestroy(t->ev);
   c->ev_en = c->ev_learn = c->turn_ws.ev = c->turn_bt.ev = nullptr;
   if (c->ev_out) hipEventDestroy(c->ev_out);
-  if (c->own) hipStreamDestroy(c->own);
+  give_own(c);
   for (hipEvent_t& e : c->ev_g) if (e) hipEventDestroy(e);
   c->ev_g[0] = c->ev_g[1] = nullptr;
   for (hipEvent_t& e : c->ev_bt) if (e) hipEventDestroy(e);
   c->ev_bt[0] = c->ev_bt[1] = nullptr;
   c->ev_in = c->ev_out = c->ev_tab = c->ev_chunk = c->ev_part = nullptr;
-  c->own = nullptr;
   void* ptrs[] = {c->d_coef, c->d_cvec, c->d_schur, c->d_U, c->d_row_chan, c->d_ch_off,
                   c->d_ch_len, c->d_ch_coef, c->d_rowinfo, c->d_runs, c->d_coefpad, c->d_schunk, c->d_sgroup, c->d_units, c->d_ucount, c->d_uowner, c->d_uw, c->d_chunk64, c->d_pairs, c->d_pair_w, c->d_pair_begin,
                   c->d_ws, c->d_dsp, c->d_gpart, c->d_dpart, c->d_vres, c->d_voff, c->d_knb,
@@ -2212,7 +2254,7 @@ exc_status exchange_init(const exc_desc* d, const exc_coulomb* cv, void* stream,
   } else {
     ITRY(configure(c, c->fused ? c->fcfg : nullptr, st));
   }
-  IHIP(hipStreamCreateWithFlags(&c->own, hipStreamNonBlocking));
+  IHIP(take_own(c));
   IHIP(hipEventCreateWithFlags(&c->ev_in, hipEventDisableTiming));
   IHIP(hipEventCreateWithFlags(&c->ev_tab, hipEventDisableTiming));
   IHIP(hipEventCreateWithFlags(&c->ev_out, hipEventDisableTiming));
